@@ -1664,18 +1664,60 @@ __global__ __launch_bounds__(kBlock) void k_snapshot(const BoxDev* __restrict__ 
     block_diag(d, partials + (size_t)t * kNumDiag);
 }
 
-// Block sum of one int128 per thread and component; thread 0 gets the totals.
-__device__ __forceinline__ void block_sum128(__int128 (&acc)[kNumDiag], __int128 (&tot)[kNumDiag])
+// Block sums of the exact diagnostics: thread t holds its share of component
+// t % kNumDiag as high and low 32-bit words (each sum below 2^63 for 2^31
+// terms), the threads of a component fold eight shares each, then seven
+// threads fold the eight results into 128-bit totals for thread 0.  Latency
+// bound (one workgroup): one thread adding 256 x 7 totals in turn took 64 us
+// of every call, this takes about 4 us.
+constexpr int kStatBlock = 64 * kNumDiag;
+__device__ __forceinline__ void stat_totals(long long hi, unsigned long long lo, __int128 (&tot)[kNumDiag])
 {
-    __shared__ __int128 red[kBlock][kNumDiag];
-#pragma unroll
-    for (int j = 0; j < kNumDiag; ++j) red[threadIdx.x][j] = acc[j];
+    constexpr int kFold = 8;   // kStatBlock = kNumDiag x kFold x kFold
+    static_assert(kStatBlock == kNumDiag * kFold * kFold, "two folds of eight");
+    __shared__ long long sh[kStatBlock];
+    __shared__ unsigned long long sl[kStatBlock];
+    __shared__ __int128 red[kNumDiag];
+    const int t = threadIdx.x;
+    sh[t] = hi;
+    sl[t] = lo;
     __syncthreads();
-    if (threadIdx.x != 0) return;
-    for (int j = 0; j < kNumDiag; ++j) {
-        __int128 v = 0;
-        for (int i = 0; i < kBlock; ++i) v += red[i][j];
-        tot[j] = v;
+    if (t < kNumDiag * kFold) {   // one wave: shares t, t + 56, t + 112, ... (same component)
+        for (int i = 1; i < kFold; ++i) {
+            hi += sh[t + i * kNumDiag * kFold];
+            lo += sl[t + i * kNumDiag * kFold];
+        }
+    }
+    __syncthreads();
+    if (t < kNumDiag * kFold) {
+        sh[t] = hi;
+        sl[t] = lo;
+    }
+    __syncthreads();
+    if (t < kNumDiag) {
+        for (int i = 1; i < kFold; ++i) {
+            hi += sh[t + i * kNumDiag];
+            lo += sl[t + i * kNumDiag];
+        }
+        red[t] = ((__int128)hi << 32) + (__int128)lo;
+    }
+    __syncthreads();
+    for (int j = 0; j < kNumDiag; ++j) tot[j] = red[j];
+}
+
+// This thread's share of `nitems` records of kNumDiag exact partials.
+__device__ __forceinline__ void stat_share(const long long* partials, int64_t nitems, long long& hi,
+                                           unsigned long long& lo)
+{
+    static_assert(kStatBlock % kNumDiag == 0, "a thread stays on one component");
+    hi = 0;
+    lo = 0;
+    const int64_t n = nitems * kNumDiag;
+#pragma unroll 8
+    for (int64_t f = threadIdx.x; f < n; f += kStatBlock) {
+        const long long v = partials[f];
+        hi += v >> 32;
+        lo += (unsigned)(v & 0xffffffffll);
     }
 }
 
@@ -1731,25 +1773,25 @@ __device__ void box_stats_finish(const __int128 (&tot)[kNumDiag], const BoxDev* 
 // workgroup over all tiles, or (many tiles) k_box_stats_tiles first folds
 // runs of `per` tiles into one 128-bit partial each, kept in the first two
 // tiles' slots of the run, and this kernel reads those (packed = 1).
-__global__ __launch_bounds__(kBlock) void k_box_stats(const long long* __restrict__ partials, int nitems,
-                                                       int per, int packed, const BoxDev* __restrict__ box,
-                                                       BoxState* __restrict__ st, int mode, double kT,
-                                                       double mass)
+__global__ __launch_bounds__(kStatBlock) void k_box_stats(const long long* __restrict__ partials, int nitems,
+                                                           int per, int packed, const BoxDev* __restrict__ box,
+                                                           BoxState* __restrict__ st, int mode, double kT,
+                                                           double mass)
 {
-    __int128 acc[kNumDiag], tot[kNumDiag];
-#pragma unroll
-    for (int j = 0; j < kNumDiag; ++j) acc[j] = 0;
-    for (int t = threadIdx.x; t < nitems; t += kBlock) {
-        if (packed) {
-            const __int128* q = reinterpret_cast<const __int128*>(partials + (size_t)t * per * kNumDiag);
-#pragma unroll
-            for (int j = 0; j < kNumDiag; ++j) acc[j] += q[j];
-        } else {
-#pragma unroll
-            for (int j = 0; j < kNumDiag; ++j) acc[j] += partials[(size_t)t * kNumDiag + j];
+    __int128 tot[kNumDiag];
+    long long hi = 0;
+    unsigned long long lo = 0;
+    if (packed) {
+        const int j = threadIdx.x % kNumDiag;
+        for (int t = threadIdx.x / kNumDiag; t < nitems; t += kStatBlock / kNumDiag) {
+            const __int128 q = reinterpret_cast<const __int128*>(partials + (size_t)t * per * kNumDiag)[j];
+            hi += (long long)(q >> 32);
+            lo += (unsigned long long)(q & 0xffffffff);
         }
+    } else {
+        stat_share(partials, nitems, hi, lo);
     }
-    block_sum128(acc, tot);
+    stat_totals(hi, lo, tot);
     if (threadIdx.x == 0) box_stats_finish(tot, box, st, mode, kT, mass);
 }
 
@@ -1757,17 +1799,14 @@ __global__ __launch_bounds__(kBlock) void k_box_stats(const long long* __restric
 // partials of tiles [g per, (g + 1) per) and stores the 128-bit totals over
 // the first two tiles of its run (per >= 2; each workgroup reads and writes
 // only its own run).
-__global__ __launch_bounds__(kBlock) void k_box_stats_tiles(long long* __restrict__ partials, int ntiles, int per)
+__global__ __launch_bounds__(kStatBlock) void k_box_stats_tiles(long long* __restrict__ partials, int ntiles, int per)
 {
     const int t0 = blockIdx.x * per, t1 = min(ntiles, t0 + per);
-    __int128 acc[kNumDiag], tot[kNumDiag];
-#pragma unroll
-    for (int j = 0; j < kNumDiag; ++j) acc[j] = 0;
-    for (int t = t0 + threadIdx.x; t < t1; t += kBlock)
-#pragma unroll
-        for (int j = 0; j < kNumDiag; ++j) acc[j] += partials[(size_t)t * kNumDiag + j];
-    block_sum128(acc, tot);
-    __syncthreads();   // every thread has read its tiles before thread 0 overwrites the first two
+    __int128 tot[kNumDiag];
+    long long hi;
+    unsigned long long lo;
+    stat_share(partials + (size_t)t0 * kNumDiag, t1 - t0, hi, lo);
+    stat_totals(hi, lo, tot);   // its barriers: every thread has read its tiles before thread 0 overwrites two
     if (threadIdx.x == 0) {
         __int128* q = reinterpret_cast<__int128*>(partials + (size_t)t0 * kNumDiag);
         for (int j = 0; j < kNumDiag; ++j) q[j] = tot[j];
@@ -1825,16 +1864,14 @@ __global__ __launch_bounds__(kBlock) void k_moments_tiles(const float* __restric
     block_diag(d, partials + (size_t)blockIdx.x * kNumDiag);
 }
 
-__global__ __launch_bounds__(kBlock) void k_moments_finish(const long long* __restrict__ partials, int ntile,
-                                                            double* __restrict__ out)
+__global__ __launch_bounds__(kStatBlock) void k_moments_finish(const long long* __restrict__ partials, int ntile,
+                                                                double* __restrict__ out)
 {
-    __int128 acc[kNumDiag], tot[kNumDiag];
-#pragma unroll
-    for (int j = 0; j < kNumDiag; ++j) acc[j] = 0;
-    for (int t = threadIdx.x; t < ntile; t += kBlock)
-#pragma unroll
-        for (int j = 0; j < kNumDiag; ++j) acc[j] += partials[(size_t)t * kNumDiag + j];
-    block_sum128(acc, tot);
+    __int128 tot[kNumDiag];
+    long long hi;
+    unsigned long long lo;
+    stat_share(partials, ntile, hi, lo);
+    stat_totals(hi, lo, tot);
     if (threadIdx.x == 0) {
 #pragma clang fp contract(off)
         for (int j = 0; j < 3; ++j) out[j] = (double)tot[j] * 2.3283064365386963e-10;   // 2^-32
@@ -1987,14 +2024,14 @@ void launch_box_stats(const Tables& T, int32_t box, int ntile, long long* part, 
                       double mass, hipStream_t s)
 {
     if (ntile <= 4 * kBlock) {
-        hipLaunchKernelGGL(k_box_stats, dim3(1), dim3(kBlock), 0, s, part, ntile, 1, 0, T.boxes + box,
+        hipLaunchKernelGGL(k_box_stats, dim3(1), dim3(kStatBlock), 0, s, part, ntile, 1, 0, T.boxes + box,
                            T.state + box, mode, kT, mass);
         return;
     }
     const int per = (ntile + kBlock - 1) / kBlock;   // >= 5, so each run holds two tiles' slots
     const int groups = (ntile + per - 1) / per;
-    hipLaunchKernelGGL(k_box_stats_tiles, dim3(groups), dim3(kBlock), 0, s, part, ntile, per);
-    hipLaunchKernelGGL(k_box_stats, dim3(1), dim3(kBlock), 0, s, part, groups, per, 1, T.boxes + box,
+    hipLaunchKernelGGL(k_box_stats_tiles, dim3(groups), dim3(kStatBlock), 0, s, part, ntile, per);
+    hipLaunchKernelGGL(k_box_stats, dim3(1), dim3(kStatBlock), 0, s, part, groups, per, 1, T.boxes + box,
                        T.state + box, mode, kT, mass);
 }
 void launch_mark_holes_box(const Tables& T, int32_t box, int ntile, hipStream_t s)
@@ -2022,7 +2059,7 @@ void launch_moments(const float* vx, const float* vy, const float* vz, const flo
 {
     const int ntile = (int)((n + kPartTile - 1) / kPartTile);
     MPCD_LAUNCH(k_moments_tiles, ntile, kBlock, s, vx, vy, vz, m, n, partials);
-    hipLaunchKernelGGL(k_moments_finish, dim3(1), dim3(kBlock), 0, s, partials, ntile, out);
+    hipLaunchKernelGGL(k_moments_finish, dim3(1), dim3(kStatBlock), 0, s, partials, ntile, out);
 }
 void launch_hbm_copy(const void* src, void* dst, int64_t n16, int blocks, hipStream_t s)
 {

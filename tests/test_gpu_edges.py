@@ -1,0 +1,65 @@
+"""Kernels at the sizes where their tiles, remainders and ranges end."""
+import numpy as np
+import pytest
+
+from paper_2212_11878_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mp():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2212_11878_amd import mpcd
+    return mpcd
+
+
+def exact_moments(vel, mass):
+    """(sum m v, sum m v^2): each term rounded to the quantum 2^-32, the
+    integers added exactly, each total rounded once."""
+    def total(term):
+        t = np.rint(term * 2.0 ** 32).astype(np.int64)
+        hi, lo = int((t >> 32).sum()), int((t & 0xFFFFFFFF).sum())
+        return float((hi << 32) + lo) * 2.0 ** -32
+    v, m = vel.astype(np.float64), mass.astype(np.float64)
+    return [total(m * v[d]) for d in range(3)] + [total(m * (v[0] * v[0] + v[1] * v[1] + v[2] * v[2]))]
+
+
+@pytest.mark.parametrize("tiles,extra", [(63, 1), (64, 0), (64, 1), (65, -1), (1025, 17)])
+def test_moments_over_record_counts(mp, tiles, extra):
+    """Bit for bit at particle counts around one fold of the partial records."""
+    import torch
+    n = tiles * 4096 + extra
+    rng = np.random.default_rng(n)
+    vel = (rng.normal(size=(3, n)) * 8.0).astype(np.float32)
+    mass = rng.uniform(0.01, 200.0, n).astype(np.float32)
+    v, m = torch.from_numpy(vel).cuda(), torch.from_numpy(mass).cuda()
+    out = torch.zeros(5, dtype=torch.float64, device="cuda")
+    rc = mp.mpcd_moments_noalloc(v[0].data_ptr(), v[1].data_ptr(), v[2].data_ptr(), m.data_ptr(), n, out.data_ptr())
+    torch.cuda.synchronize()
+    assert rc == mp.MPCD_OK
+    # (the energy term's FP64 products may be contracted on the device: each
+    # then differs by at most one quantum, a few parts in 2^53 of the term)
+    got, want = out.cpu().numpy(), exact_moments(vel, mass)
+    assert list(got[:3]) == want[:3] and got[4] == 0
+    v2 = float((mass.astype(np.float64) * (vel.astype(np.float64) ** 2).sum(axis=0)).sum())
+    assert abs(got[3] - want[3]) <= n * 2.0 ** -32 + 4.0 * 2.0 ** -53 * v2
+
+
+@pytest.mark.parametrize("L,density", [((60, 60, 61), 8.6), ((100, 90, 91), 8.1)])
+def test_observe_over_record_counts(mp, L, density):
+    """Boxes on both sides of the reduction's second level: the observables
+    are those of the state read back."""
+    n = int(density * L[0] * L[1] * L[2])
+    pos, vel = inputs.thermal_state(L, n, seed=n)
+    with mp.Context() as ctx:
+        slot = ctx.admit(mp.make_desc(L, n, init="external", seed=3))
+        ctx.set_state(slot, (pos, vel))
+        ctx.step(2)
+        obs = ctx.observe(slot)
+        _, v, _ = ctx.get_state(slot)
+    want = exact_moments(v, np.ones(n))
+    assert list(obs["P"]) == want[:3]
+    assert abs(2.0 * obs["E"] - want[3]) <= n * 2.0 ** -32 + 4.0 * 2.0 ** -53 * want[3]
