@@ -143,6 +143,23 @@ __device__ __forceinline__ void step_flush(const long long (&d)[kNumDiag], bool 
     if (any && threadIdx.x == 0) gatomic_add(gp(a) + 2, 1ll);
 }
 
+// The same without a workgroup barrier: each wave adds its own share of the
+// VACF sum (at most 4096 terms below 3 2^48) and its range-violation mark.
+__device__ __forceinline__ void step_flush_wave(long long viol, long long vsum, bool vacf, long long* acc,
+                                                int lane_sel)
+{
+    long long* a = acc + (size_t)(lane_sel & (kAccLanes - 1)) * 3;
+    const int lane = threadIdx.x & (kWave - 1);
+    if (vacf) {
+        const long long v = wave_sum(vsum);
+        if (lane == 0) {
+            gatomic_add(gp(a), v >> 32);
+            gatomic_add(gp(a) + 1, (long long)(unsigned long long)(unsigned)(v & 0xffffffffll));
+        }
+    }
+    if (__any(viol != 0) && lane == 0) gatomic_add(gp(a) + 2, 1ll);
+}
+
 // Block-wide exclusive scan of one uint32 per thread; returns the prefix and
 // the block total in *total.
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* total)
@@ -271,13 +288,54 @@ __device__ __forceinline__ void vacf_term(const BoxDev& b, int32_t id, float3 v,
     diag_vacf(d, v, w.x, w.y, w.z);
 }
 
+// The lowest u of `mask` selects one of this thread's kS register values.
+template <int kS, class T>
+__device__ __forceinline__ T pick(const T (&a)[kS], int u)
+{
+    T r = a[0];
+#pragma unroll
+    for (int i = 1; i < kS; ++i) {
+        const T v = a[i];
+        r = u == i ? v : r;
+    }
+    return r;
+}
+template <int kS, class T>
+__device__ __forceinline__ void put(T (&a)[kS], int u, T v)
+{
+#pragma unroll
+    for (int i = 0; i < kS; ++i) {
+        const T old = a[i];
+        a[i] = u == i ? v : old;
+    }
+}
+
+// x in [0, len), written as one comparison of the bits (a negative x, -0 and
+// a NaN compare above every length)
+__device__ __forceinline__ bool inside(float x, float len)
+{
+    return __float_as_uint(x) < __float_as_uint(len);
+}
+
+// Term of an exact cell sum held in FP64: v 2^32 truncated toward zero, the
+// value of to_fixed(v).  Below the velocity limit a term is an integer below
+// 2^40 and a cell of fewer than kMaxCellCount terms sums to less than 2^52, so
+// FP64 additions are exact in any order and give the integer sum.  (The clamp
+// keeps a velocity that is not finite out of the cell's sum; its box is
+// marked.)
+__device__ __forceinline__ double exact_term(float v)
+{
+    constexpr float kQ = 4294967296.0f, kTop = kVelocityLimit * kQ;
+    return (double)truncf(__builtin_amdgcn_fmed3f(v * kQ, -kTop, kTop));
+}
+
 // One SRD step of one brick (paper Sec. 2; the shifted grid of Sec. 3.1;
 // the mass-weighted cell velocity of Sec. 3.3).  The workgroup owns every
 // particle whose collision cell lies in its brick, so the whole step is one
 // pass over them, held in registers (kS per thread; larger buckets take
 // several chunks, re-read from memory):
-//   1. stream, collision cell, exact fixed-point cell sums in LDS
-//      (+ escape sums of overflow particles, when flagged)
+//   1. stream, collision cell, exact cell sums in LDS (+ escape sums of
+//      overflow particles, when flagged)
 //   2. per cell: u_c = sum(m v)/sum(m), axis n_c from Philox (in place)
 //   3. rotate v about n_c relative to u_c; collision cell of the next step;
 //      rank in the destination group (27 neighbour bricks: wave ballots for
@@ -285,14 +343,433 @@ __device__ __forceinline__ void vacf_term(const BoxDev& b, int32_t id, float3 v,
 //   4. one global reservation per group in the destination buckets, then
 //      stores.  Per step only the range check (and the VACF sum when a
 //      sample is due) is reduced; momentum and energy are summed on demand.
-// The instance for equal masses without particle ids (the benchmark's) is
-// held to 5 waves per SIMD (96 registers, a few spilled): measured 6 %
-// faster than 4 waves with no spill, while 6 waves (80 registers) and the
-// instances with ids at 5 waves are slower.
-template <int kT, int kS, bool kMass, bool kAM, bool kWide, bool kIds>
+// Each phase first takes the common case of every slot without a branch (the
+// particle stays inside the box and its cell needs no periodic wrap); the
+// slots that fail it are redone one at a time by a loop that holds the only
+// copy of the exact general form.  With a fold, a wrap and a far branch in
+// line for every slot and coordinate the kernel had twice the instructions
+// (58 KB of code): 256^3 box without ids 2.02 -> 1.97 ms a step, 203 x 167 x
+// 131 cells with ids 0.528 -> 0.49 ms, 100^3 with ids 157 -> 145 us.  What
+// bounds it is HBM: 48 B a particle, and the workgroup's chain of loads, cell
+// sums, reservation and stores, of which 5 per CU overlap.
+// The instance for equal masses without particle ids is held to 5 waves per
+// SIMD (96 registers), those with ids or 8 slots per thread to 4.
+template <int kT, int kS, bool kMass, bool kWide, bool kIds>
 __global__ __launch_bounds__(kT)
-__attribute__((amdgpu_waves_per_eu(kMass || kAM ? 1 : (kIds || kS > 6 ? 4 : 5), kMass || kAM || kIds || kS > 6 ? 8 : 5)))
+__attribute__((amdgpu_waves_per_eu(kMass ? 1 : (kIds || kS > 6 ? 4 : 5), kMass || kIds || kS > 6 ? 8 : 5)))
 void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __restrict__ boxes,
+                  const BoxState* __restrict__ st, long long* __restrict__ dacc)
+{
+    // LDS, per cell of the brick: exact sums of m v and of m in 40-byte
+    // records (equal masses: three FP64 sums and a 32-bit count; per-particle
+    // masses: four 64-bit integers and a count), then the collision map in
+    // 48-byte records (three 16-byte reads); both strides spread neighbouring
+    // cells over the LDS banks.
+    extern __shared__ __align__(16) unsigned long long lds64[];
+    constexpr int kWaves = kT / kWave;
+    // destination groups: 27 neighbour bricks (13 = this one), then the
+    // particles of each wave that stay, in one run per wave
+    __shared__ uint32_t gcnt[27 + kWaves];
+    __shared__ uint2 gslot[27 + kWaves];      // first slot of the group, end of its bucket
+    constexpr uint32_t kChunk = (uint32_t)kT * kS;
+    constexpr uint32_t kNone = 0xffffffffu;   // no particle / no cell
+    constexpr uint32_t kFar = 63u;            // destination beyond the neighbours
+    constexpr uint32_t kIdle = 62u;           // no particle in the slot
+    const int t = xcd_tile(blockIdx.x, gridDim.x);
+    // with a single brick box the brick tiles are its bricks in order, and
+    // the tile record need not be loaded before the box's
+    const Tile tl = one_box >= 0 ? Tile{one_box, 0, t, t + 1} : tiles[t];
+    const BoxState s = st[uniform(tl.box)];
+    const BoxDev& b = boxes[uniform(tl.box)];
+    if (box_idle(s) || b.binning != 1) return;
+    const int brick = uniform((int)tl.begin);
+    const long long k = uniform(s.k);
+    const int src = uniform(s.parity), dst = src ^ 1;
+    const int nb0 = b.nb[0], nb1 = b.nb[1], nb2 = b.nb[2];
+    const int bx = brick % nb0, by = (brick / nb0) % nb1, bz = brick / (nb0 * nb1);
+    const int lox = brick_lo(bx, b.bshift[0]), loy = brick_lo(by, b.bshift[1]), loz = brick_lo(bz, b.bshift[2]);
+    const int ex = min(1 << b.bshift[0], b.L[0] - lox);
+    const int ey = min(1 << b.bshift[1], b.L[1] - loy);
+    const int ez = min(1 << b.bshift[2], b.L[2] - loz);
+    const int ncl = ex * ey * ez;
+    unsigned long long* const acc = lds64;   // [ncl][kAccWords]
+    float* const fu = reinterpret_cast<float*>(lds64 + ((kAccWords * ncl + 1) & ~1));   // [ncl][kUnWords]
+    for (int i = threadIdx.x; i < kAccWords * ncl; i += kT) lds64[i] = 0ull;
+    const uint32_t beg = (uint32_t)uniform((int)gp(b.bstart)[brick]);
+    // escape sums for this brick (overflow particles of the previous step):
+    // flagged during that step, in the half of eflag this step only reads,
+    // so the load goes out with the bucket's and is not waited for here
+    const uint32_t stamp = (uint32_t)(k + 1);
+    const uint32_t eflag_k = gp(b.eflag)[(size_t)(k & 1) * b.nbrick + brick];
+    // the bucket's fill, read by every wave (this workgroup alone reads it and
+    // clears it, since this buffer is the next step's destination)
+    const uint32_t cnt = min((uint32_t)uniform((int)gp(b.bsize[src])[brick]),
+                             (uint32_t)uniform((int)gp(b.bstart)[brick + 1]) - beg);
+    __syncthreads();
+    if (threadIdx.x == 0) gp(b.bsize[src])[brick] = 0u;   // every wave has read it
+    const int nch = (int)((cnt + kChunk - 1) / kChunk);
+
+    // bucket-relative bases (uniform): a lane's offset is its index in the bucket
+    const MPCD_G float* __restrict__ ix = ugp(b.p[src][0]) + beg;
+    const MPCD_G float* __restrict__ iy = ugp(b.p[src][1]) + beg;
+    const MPCD_G float* __restrict__ iz = ugp(b.p[src][2]) + beg;
+    const MPCD_G float* __restrict__ ivx = ugp(b.p[src][3]) + beg;
+    const MPCD_G float* __restrict__ ivy = ugp(b.p[src][4]) + beg;
+    const MPCD_G float* __restrict__ ivz = ugp(b.p[src][5]) + beg;
+    const bool has_mass = kMass && b.m[src] != nullptr;   // uniform
+    const MPCD_G float* __restrict__ im = has_mass ? ugp(b.m[src]) + beg : nullptr;
+    const float3 sh = grid_shift(b, k);
+    const float dt = b.dt;
+    const float inv_a = b.inv_a;
+    const float len0 = b.len[0], len1 = b.len[1], len2 = b.len[2];
+
+    float px[kS], py[kS], pz[kS], vx[kS], vy[kS], vz[kS], pm[kMass ? kS : 1];
+    uint32_t meta[kS];   // cell in the brick after loading; destination group << 24 | rank later
+    long long viol = 0;
+    auto mass_at = [&](int u) -> float { return kMass ? pick(pm, u) : 1.0f; };
+    // slots of chunk ch that hold particles for some thread (uniform)
+    auto used_slots = [&](int ch) -> int {
+        const uint32_t rem = cnt - (uint32_t)ch * kChunk;
+        return (int)min((uint32_t)kS, (rem + kT - 1) / kT);
+    };
+    auto index_of = [&](int ch, int u) -> uint32_t {
+        return (uint32_t)ch * kChunk + (uint32_t)(u * kT) + threadIdx.x;
+    };
+    // load and stream chunk ch; meta <- cell inside the brick, kNone past the
+    // end of the bucket or for a particle in the wrong bucket (never happens:
+    // both sides use the same arithmetic; flagged if it does)
+    auto load = [&](int ch) {
+        const int nu = used_slots(ch);
+#pragma unroll
+        for (int u = 0; u < kS; ++u) {   // issue every load first
+            if (u >= nu) break;
+            const uint32_t i = index_of(ch, u);
+            const uint32_t o = (i < cnt ? i : 0u) * 4u;   // byte offset inside the bucket
+            px[u] = ldg(ix, o);
+            py[u] = ldg(iy, o);
+            pz[u] = ldg(iz, o);
+            vx[u] = ldg(ivx, o);
+            vy[u] = ldg(ivy, o);
+            vz[u] = ldg(ivz, o);
+            if (kMass) pm[u] = has_mass ? ldg(im, o) : 1.0f;
+        }
+        uint32_t redo = 0u;
+#pragma unroll
+        for (int u = 0; u < kS; ++u) {
+            meta[u] = kNone;
+            if (u >= nu) continue;
+            const uint32_t i = index_of(ch, u);
+            px[u] = fmaf(vx[u], dt, px[u]);
+            py[u] = fmaf(vy[u], dt, py[u]);
+            pz[u] = fmaf(vz[u], dt, pz[u]);
+            const int cx = (int)floorf((px[u] - sh.x) * inv_a) - lox;
+            const int cy = (int)floorf((py[u] - sh.y) * inv_a) - loy;
+            const int cz = (int)floorf((pz[u] - sh.z) * inv_a) - loz;
+            const bool in = (unsigned)cx < (unsigned)ex && (unsigned)cy < (unsigned)ey && (unsigned)cz < (unsigned)ez &&
+                            inside(px[u], len0) && inside(py[u], len1) && inside(pz[u], len2);
+            if (i < cnt) {
+                meta[u] = in ? (uint32_t)(cx + ex * (cy + ey * cz)) : kNone;
+                redo |= in ? 0u : 1u << u;
+            }
+        }
+        while (redo) {   // periodic images, in the exact general form
+            const int u = __ffs((int)redo) - 1;
+            redo &= redo - 1u;
+            const float x = fold(pick(px, u), len0), y = fold(pick(py, u), len1), z = fold(pick(pz, u), len2);
+            const int cx = axis_cell_raw(x, sh.x, inv_a, b.L[0]) - lox;   // range-checked below
+            const int cy = axis_cell_raw(y, sh.y, inv_a, b.L[1]) - loy;
+            const int cz = axis_cell_raw(z, sh.z, inv_a, b.L[2]) - loz;
+            const bool in = (unsigned)cx < (unsigned)ex && (unsigned)cy < (unsigned)ey && (unsigned)cz < (unsigned)ez;
+            put(px, u, x);
+            put(py, u, y);
+            put(pz, u, z);
+            put(meta, u, in ? (uint32_t)(cx + ex * (cy + ey * cz)) : kNone);
+            if (!in) viol += 1;
+        }
+    };
+
+    // 1. cell sums; the last chunk first, so that chunk 0 stays in registers
+    for (int ch = nch - 1; ch >= 0; --ch) {
+        load(ch);
+#pragma unroll
+        for (int u = 0; u < kS; ++u) {
+            const uint32_t c = meta[u];
+            if (c == kNone) continue;
+            unsigned long long* const r = acc + c * kAccWords;
+            if (kMass) {
+                const float mi = pm[u];
+                atomicAdd(&r[0], to_fixed(mi * vx[u]));
+                atomicAdd(&r[1], to_fixed(mi * vy[u]));
+                atomicAdd(&r[2], to_fixed(mi * vz[u]));
+                atomicAdd(&r[3], to_fixed(mi));
+                atomicAdd(reinterpret_cast<uint32_t*>(&r[4]), 1u);   // particle count
+            } else {   // equal masses: r[3] counts particles
+                double* const rd = reinterpret_cast<double*>(r);
+                unsafeAtomicAdd(&rd[0], exact_term(vx[u]));
+                unsafeAtomicAdd(&rd[1], exact_term(vy[u]));
+                unsafeAtomicAdd(&rd[2], exact_term(vz[u]));
+                atomicAdd(reinterpret_cast<uint32_t*>(&r[3]), 1u);
+            }
+        }
+    }
+    if (threadIdx.x < 27 + kWaves) gcnt[threadIdx.x] = 0u;
+    __syncthreads();
+    const bool flagged = eflag_k == stamp;
+    const uint32_t L0 = (uint32_t)b.L[0], L01 = (uint32_t)b.L[0] * (uint32_t)b.L[1];
+    if (flagged) {   // overflow particles of this step whose cells lie here
+        MPCD_G CellAcc* __restrict__ esc = gp(b.esc[k & 1]);
+        for (int c = threadIdx.x; c < ncl; c += kT) {
+            const int lx = c % ex, ly = (c / ex) % ey, lz = c / (ex * ey);
+            const uint32_t gc = (uint32_t)(lox + lx) + L0 * (uint32_t)(loy + ly) + L01 * (uint32_t)(loz + lz);
+            const CellAcc e = load_acc(esc + gc);
+            if (e.w) {
+                unsigned long long* const r = acc + c * kAccWords;
+                if (kMass) {
+                    r[0] += e.sx;
+                    r[1] += e.sy;
+                    r[2] += e.sz;
+                    r[3] += e.w;
+                    if (has_mass) {   // and their count
+                        MPCD_G uint32_t* const ec = gp(b.ecnt[k & 1]) + gc;
+                        *reinterpret_cast<uint32_t*>(&r[4]) += *ec;
+                        *ec = 0u;
+                    }
+                } else {
+                    double* const rd = reinterpret_cast<double*>(r);
+                    rd[0] += fixed_to_double(e.sx);   // integers below 2^52: exact
+                    rd[1] += fixed_to_double(e.sy);
+                    rd[2] += fixed_to_double(e.sz);
+                    r[3] += e.w >> 32;   // escape weights are 2^32 m
+                }
+                CellAcc z = {0ull, 0ull, 0ull, 0ull};
+                store_acc(esc + gc, z);
+            }
+        }
+        __syncthreads();
+    }
+
+    // 2. cell velocity and axis
+    for (int c = threadIdx.x; c < ncl; c += kT) {
+        const unsigned long long* const r = acc + c * kAccWords;
+        const unsigned long long w = kMass ? r[3] : ((r[3] & 0xffffffffull) << 32);
+        if (w == 0) continue;
+        const uint32_t count = kMass ? (uint32_t)r[4] : (uint32_t)r[3];
+        if (count >= kMaxCellCount) viol += 1;   // the cell's sums may have wrapped
+        const int lx = c % ex, ly = (c / ex) % ey, lz = c / (ex * ey);
+        const uint32_t gc = (uint32_t)(lox + lx) + L0 * (uint32_t)(loy + ly) + L01 * (uint32_t)(loz + lz);
+        double uc[3];
+        if (kMass) {
+            fixed_mean3(r[0], r[1], r[2], w, uc);
+        } else {
+#pragma clang fp contract(off)
+            const double* const rd = reinterpret_cast<const double*>(r);
+            const double inv = 1.0 / fixed_to_double(w);
+            uc[0] = rd[0] * inv;
+            uc[1] = rd[1] * inv;
+            uc[2] = rd[2] * inv;
+        }
+        const CellRot cr = cell_rotation(uc[0], uc[1], uc[2], cell_axis(b, k, gc), b.ca, b.sa);
+        float4* const q = reinterpret_cast<float4*>(fu + c * kUnWords);
+        q[0] = make_float4(cr.m[0], cr.m[1], cr.m[2], cr.m[3]);
+        q[1] = make_float4(cr.m[4], cr.m[5], cr.m[6], cr.m[7]);
+        q[2] = make_float4(cr.m[8], cr.t[0], cr.t[1], cr.t[2]);
+        if (flagged) store_rot(gp(b.un) + gc, cr);   // read by the overflow particles
+    }
+    __syncthreads();
+
+    // 3./4. rotate, route to the next step's buckets, store
+    const float3 sh1 = grid_shift(b, k + 1);
+    // A particle inside the box whose next cell i = floor((x' - s1)/a) lies,
+    // along every axis, in [0, L) and in this brick or one next to it (no
+    // periodic wrap) goes to neighbour (i >> shift) - b; one comparison
+    // against the cells [n0, n0 + nw) of those bricks tests all of it.  The
+    // others (images, far ones, non-finite positions) take the exact form.
+    const int n00 = max(bx - 1, 0) << b.bshift[0], n01 = max(by - 1, 0) << b.bshift[1],
+              n02 = max(bz - 1, 0) << b.bshift[2];
+    const unsigned nw0 = (unsigned)(min((bx + 2) << b.bshift[0], b.L[0]) - n00),
+                   nw1 = (unsigned)(min((by + 2) << b.bshift[1], b.L[1]) - n01),
+                   nw2 = (unsigned)(min((bz + 2) << b.bshift[2], b.L[2]) - n02);
+    // group of the neighbour at offset (-1, -1, -1) of cells from n0 on
+    const uint32_t g0 = (bx == 0 ? 1u : 0u) + (by == 0 ? 3u : 0u) + (bz == 0 ? 9u : 0u);
+    MPCD_G float* const ox = ugp(b.p[dst][0]);
+    MPCD_G float* const oy = ugp(b.p[dst][1]);
+    MPCD_G float* const oz = ugp(b.p[dst][2]);
+    MPCD_G float* const ovx = ugp(b.p[dst][3]);
+    MPCD_G float* const ovy = ugp(b.p[dst][4]);
+    MPCD_G float* const ovz = ugp(b.p[dst][5]);
+    const bool has_id = kIds && b.pid[src] != nullptr;   // uniform
+    MPCD_G int32_t* const oid = has_id ? ugp(b.pid[dst]) : nullptr;
+    const MPCD_G int32_t* const iid = has_id ? ugp(b.pid[src]) + beg : nullptr;   // bucket-relative
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t wave = (uint32_t)uniform((int)(threadIdx.x / kWave));
+    const unsigned long long below = (1ull << lane) - 1ull;
+    long long vsum = 0;   // VACF terms
+    const bool vacf = kIds && b.vacf_stride > 0 && ((k + 1 - uniform(s.vacf_origin)) % b.vacf_stride) == 0;
+    for (int ch = 0; ch < nch; ++ch) {
+        if (ch > 0) {
+            load(ch);
+            if (threadIdx.x < 27 + kWaves) gcnt[threadIdx.x] = 0u;
+            __syncthreads();
+        }
+        const int nu = used_slots(ch);
+        uint32_t redo = 0u, nstay = 0u;   // nstay: uniform over the wave
+        float vmax = 0.0f;
+#pragma unroll
+        for (int u = 0; u < kS; ++u) {
+            const uint32_t c = meta[u];
+            meta[u] = kIdle << 24;
+            if (u >= nu) continue;
+            const uint32_t i = index_of(ch, u);
+            bool stay = false;
+            if (i < cnt) {
+                if (c != kNone) {
+                    const float4* const q = reinterpret_cast<const float4*>(fu + c * kUnWords);
+                    const float4 q0 = q[0], q1 = q[1], q2 = q[2];
+                    CellRot cr;
+                    cr.m[0] = q0.x; cr.m[1] = q0.y; cr.m[2] = q0.z; cr.m[3] = q0.w;
+                    cr.m[4] = q1.x; cr.m[5] = q1.y; cr.m[6] = q1.z; cr.m[7] = q1.w;
+                    cr.m[8] = q2.x; cr.t[0] = q2.y; cr.t[1] = q2.z; cr.t[2] = q2.w;
+                    const float3 v = apply_rotation(cr, vx[u], vy[u], vz[u]);
+                    vx[u] = v.x;
+                    vy[u] = v.y;
+                    vz[u] = v.z;
+                }
+                // (a NaN drops out of the maximum; its position fails `inside`)
+                vmax = fmaxf(fmaxf(vmax, fabsf(vx[u])), fmaxf(fabsf(vy[u]), fabsf(vz[u])));
+                const float qx = fmaf(vx[u], dt, px[u]), qy = fmaf(vy[u], dt, py[u]), qz = fmaf(vz[u], dt, pz[u]);
+                const unsigned dx = (unsigned)((int)floorf((qx - sh1.x) * inv_a) - n00);
+                const unsigned dy = (unsigned)((int)floorf((qy - sh1.y) * inv_a) - n01);
+                const unsigned dz = (unsigned)((int)floorf((qz - sh1.z) * inv_a) - n02);
+                const bool near = dx < nw0 && dy < nw1 && dz < nw2 && inside(qx, len0) && inside(qy, len1) &&
+                                  inside(qz, len2);
+                const uint32_t r = g0 + (dx >> b.bshift[0]) + 3u * (dy >> b.bshift[1]) + 9u * (dz >> b.bshift[2]);
+                stay = near && r == 13u;
+                if (!near) redo |= 1u << u;
+                else if (!stay) meta[u] = (r << 24) | atomicAdd(&gcnt[r], 1u);
+            }
+            // particles that stay in the brick (most) take consecutive ranks
+            // per wave, so their stores coalesce
+            const unsigned long long mask = __ballot(stay);
+            if (stay) meta[u] = ((27u + wave) << 24) | (nstay + (uint32_t)__popcll(mask & below));
+            nstay += (uint32_t)__popcll(mask);
+        }
+        if (lane == 0) gcnt[27u + wave] = nstay;
+        if (!(vmax < kVelocityLimit)) viol += 1;
+        while (redo) {   // periodic images and far destinations, in the exact general form
+            const int u = __ffs((int)redo) - 1;
+            redo &= redo - 1u;
+            const float3 v = make_float3(pick(vx, u), pick(vy, u), pick(vz, u));
+            if (!in_range(v)) viol += 1;
+            const float qx = fold(fmaf(v.x, dt, pick(px, u)), len0);
+            const float qy = fold(fmaf(v.y, dt, pick(py, u)), len1);
+            const float qz = fold(fmaf(v.z, dt, pick(pz, u)), len2);
+            const int rx = brick_rel(bx, brick_of(axis_cell_raw(qx, sh1.x, inv_a, b.L[0]), b.bshift[0]), nb0);
+            const int ry = brick_rel(by, brick_of(axis_cell_raw(qy, sh1.y, inv_a, b.L[1]), b.bshift[1]), nb1);
+            const int rz = brick_rel(bz, brick_of(axis_cell_raw(qz, sh1.z, inv_a, b.L[2]), b.bshift[2]), nb2);
+            uint32_t r = kFar, rank = 0u;
+            if ((unsigned)(rx + 1) <= 2u && (unsigned)(ry + 1) <= 2u && (unsigned)(rz + 1) <= 2u) {
+                r = (uint32_t)((rx + 1) + 3 * ((ry + 1) + 3 * (rz + 1)));
+                rank = atomicAdd(&gcnt[r], 1u);
+            }
+            put(meta, u, (r << 24) | rank);
+        }
+        // identities (only needed for the store): load while the groups reserve
+        int32_t id[kIds ? kS : 1];
+        if (has_id) {
+#pragma unroll
+            for (int u = 0; u < kS; ++u) {
+                if (u >= nu) break;
+                const uint32_t i = index_of(ch, u);
+                if (kIds) id[u] = ldg(iid, (i < cnt ? i : 0u) * 4u);
+            }
+        }
+        __syncthreads();
+        if (threadIdx.x < 27) {
+            const int q = threadIdx.x;
+            uint32_t n = gcnt[q], runs = 0u;
+            if (q == 13)
+                for (int w = 0; w < kWaves; ++w) runs += gcnt[27 + w];
+            if (n + runs) {
+                const int dx = brick_nbr(bx, q % 3 - 1, nb0), dy = brick_nbr(by, (q / 3) % 3 - 1, nb1),
+                          dz = brick_nbr(bz, q / 9 - 1, nb2);
+                const uint32_t dest = (uint32_t)(dx + nb0 * (dy + nb1 * dz));
+                const uint32_t pos = gatomic_add(gp(b.bsize[dst]) + dest, n + runs);
+                const uint32_t b0 = gp(b.bstart)[dest], b1 = gp(b.bstart)[dest + 1];
+                // a reservation beyond the bucket's end leaves its slots to the overflow
+                uint32_t first = pos < b1 - b0 ? b0 + pos : b1;
+                if (q == 13)
+                    for (int w = 0; w < kWaves; ++w) {
+                        gslot[27 + w] = make_uint2(first, b1);
+                        const uint32_t nw = gcnt[27 + w];
+                        first = nw < b1 - first ? first + nw : b1;
+                    }
+                gslot[q] = make_uint2(first, b1);
+            }
+        }
+        __syncthreads();
+        // byte offset of a destination slot (64-bit for buffers of 2^30 slots or more)
+        typedef typename std::conditional<kWide, unsigned long long, uint32_t>::type Off;
+        auto store_at = [&](uint32_t j, float x, float y, float z, float3 v, int32_t pid, float m) {
+            const Off o = (Off)j * 4u;
+            stg(ox, o, x);
+            stg(oy, o, y);
+            stg(oz, o, z);
+            stg(ovx, o, v.x);
+            stg(ovy, o, v.y);
+            stg(ovz, o, v.z);
+            if (has_id) stg(oid, o, pid);
+            if (has_mass) stg(gp(b.m[dst]), o, m);
+        };
+        uint32_t miss = 0u;
+#pragma unroll
+        for (int u = 0; u < kS; ++u) {
+            if (u >= nu) break;
+            const uint32_t r = meta[u] >> 24;
+            if (r == kIdle) continue;
+            const uint2 g = gslot[r == kFar ? 0u : r];
+            const uint32_t rank = meta[u] & 0xffffffu;
+            if (r != kFar && rank < g.y - g.x)
+                store_at(g.x + rank, px[u], py[u], pz[u], make_float3(vx[u], vy[u], vz[u]), kIds ? id[u] : 0,
+                         kMass ? pm[u] : 1.0f);
+            else
+                miss |= 1u << u;
+        }
+        if (kIds && vacf) {
+#pragma unroll
+            for (int u = 0; u < kS; ++u) {
+                if (u >= nu) break;
+                if (index_of(ch, u) >= cnt) continue;
+                long long d[kNumDiag] = {};
+                vacf_term(b, id[u], make_float3(vx[u], vy[u], vz[u]), d);
+                vsum += d[4];
+            }
+        }
+        while (miss) {   // far (or full) destination, one at a time
+            const int u = __ffs((int)miss) - 1;
+            miss &= miss - 1u;
+            const float x = pick(px, u), y = pick(py, u), z = pick(pz, u);
+            const float3 v = make_float3(pick(vx, u), pick(vy, u), pick(vz, u));
+            const float m = mass_at(u);
+            const int3 nc = next_cell(b, x, y, z, v, sh1);
+            const int3 db = brick_of_cell(b, nc);
+            uint32_t j = 0u;
+            bool placed = false;
+            if ((pick(meta, u) >> 24) == kFar)
+                placed = place_single(b, dst, (uint32_t)(db.x + nb0 * (db.y + nb1 * db.z)), &j);
+            if (!placed) placed = place_overflow(b, dst, k, nc, m, v, &j);
+            if (placed) store_at(j, x, y, z, v, kIds ? pick(id, u) : 0, m);
+            else viol += 1;
+        }
+        if (ch + 1 < nch) __syncthreads();
+    }
+    step_flush_wave(viol, vsum, vacf, dacc + (size_t)uniform(tl.box) * kAccLanes * 3, blockIdx.x);
+}
+
+// The same step for launches that hold a box with the angular-momentum rule
+// (boxes without it, with and without masses and ids, are served as well).
+template <int kT, int kS>
+__global__ __launch_bounds__(kT)
+void k_brick_step_am(const Tile* __restrict__ tiles, int one_box, const BoxDev* __restrict__ boxes,
                   const BoxState* __restrict__ st, long long* __restrict__ dacc)
 {
     // LDS, per cell of the brick: exact sums of m v (3 x 64 bit) and of m (64
@@ -300,6 +777,7 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
     // n_c and kappa in 48-byte records (two 16-byte reads); both strides
     // spread neighbouring cells over the LDS banks.  Boxes with the
     // angular-momentum rule (kAM instances only) use kAmWords per cell instead.
+    constexpr bool kMass = true, kAM = true, kWide = true, kIds = true;
     extern __shared__ __align__(16) unsigned long long lds64[];
     __shared__ uint32_t gcnt[27], gpos[27], gbeg[27], gcap[27];
     constexpr uint32_t kChunk = (uint32_t)kT * kS;
@@ -1911,17 +2389,27 @@ __global__ __launch_bounds__(kBlock) void k_hbm_copy(const f32x4* __restrict__ s
         if ((grid) > 0) hipLaunchKernelGGL(kern, dim3(grid), dim3(block), 0, stream, __VA_ARGS__); \
     } while (0)
 
-template <int kT, int kS, bool kMass, bool kAM, bool kWide, bool kIds>
+template <class K>
+static void brick_step_launch(K kern, int threads, bool& attr, const Tables& T, hipStream_t s)
+{
+    if (!attr) {   // the largest brick record (kMaxBrickCells or kMaxAmBrickCells cells)
+        (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
+        attr = true;
+    }
+    hipLaunchKernelGGL(kern, dim3(T.nbtiles), dim3(threads), T.brick_lds + 16, s, T.btiles, T.brick_box, T.boxes,
+                       T.state, T.dacc);
+}
+template <int kT, int kS, bool kMass, bool kWide, bool kIds>
 static void brick_step_run(const Tables& T, hipStream_t s)
 {
     static bool attr = false;
-    if (!attr) {   // the largest brick record (kMaxBrickCells or kMaxAmBrickCells cells)
-        (void)hipFuncSetAttribute((const void*)k_brick_step<kT, kS, kMass, kAM, kWide, kIds>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
-        attr = true;
-    }
-    hipLaunchKernelGGL((k_brick_step<kT, kS, kMass, kAM, kWide, kIds>), dim3(T.nbtiles), dim3(kT), T.brick_lds + 16,
-                       s, T.btiles, T.brick_box, T.boxes, T.state, T.dacc);
+    brick_step_launch(k_brick_step<kT, kS, kMass, kWide, kIds>, kT, attr, T, s);
+}
+template <int kT, int kS>
+static void brick_step_run_am(const Tables& T, hipStream_t s)
+{
+    static bool attr = false;
+    brick_step_launch(k_brick_step_am<kT, kS>, kT, attr, T, s);
 }
 // Instances: plain without particle ids, plain and per-particle masses with
 // 32-bit store offsets (every brick buffer below 2^30 slots), masses with
@@ -1931,11 +2419,11 @@ static void brick_step_run(const Tables& T, hipStream_t s)
 template <int kT, int kS>
 static void brick_step_at(const Tables& T, hipStream_t s)
 {
-    if (T.brick_am) brick_step_run<kT, kS, true, true, true, true>(T, s);
-    else if (T.brick_wide) brick_step_run<kT, kS, true, false, true, true>(T, s);
-    else if (T.brick_mass) brick_step_run<kT, kS, true, false, false, true>(T, s);
-    else if (T.brick_ids) brick_step_run<kT, kS, false, false, false, true>(T, s);
-    else brick_step_run<kT, kS, false, false, false, false>(T, s);
+    if (T.brick_am) brick_step_run_am<kT, kS>(T, s);
+    else if (T.brick_wide) brick_step_run<kT, kS, true, true, true>(T, s);
+    else if (T.brick_mass) brick_step_run<kT, kS, true, false, true>(T, s);
+    else if (T.brick_ids) brick_step_run<kT, kS, false, false, true>(T, s);
+    else brick_step_run<kT, kS, false, false, false>(T, s);
 }
 
 // Launch shapes of the brick step (workgroup size, particles per thread),
