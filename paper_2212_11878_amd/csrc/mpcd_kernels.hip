@@ -75,7 +75,7 @@ __device__ __forceinline__ bool sort_due(const BoxDev& b, const BoxState& s)
 // cells (SORT), n plus slack for bricks (brick boxes re-bucketing).
 __device__ __forceinline__ uint32_t key_capacity(const BoxDev& b, int64_t c, uint32_t n)
 {
-    return (b.binning == 1 && c < b.nbrick) ? n + bucket_slack(n) : n;
+    return (b.binning == 1 && c < b.nbrick) ? bucket_capacity(n) : n;
 }
 
 __device__ __forceinline__ bool vacf_due(const BoxDev& b, const BoxState& s)
