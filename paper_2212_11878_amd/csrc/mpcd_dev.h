@@ -147,6 +147,14 @@ struct BoxState {
     float adj[4];          // initial-state adjustment v <- (v - adj[0..2]) * adj[3]
 };
 
+// What mpcd_observe reads, written by the device into pinned host memory: the
+// box state and its first kReportVacf VACF samples.
+constexpr int kReportVacf = 4096;
+struct BoxReport {
+    BoxState st;
+    double vacf[kReportVacf];
+};
+
 // Record copies to and from global memory as native vectors (struct
 // assignment is not defined across address spaces).
 typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));

@@ -83,6 +83,8 @@ struct mpcd_ctx {
     bool pending_rebucket = false;
     int* host_flag = nullptr;        // pinned: set by the device when a brick box needs re-bucketing
     int* host_flag_dev = nullptr;    // its device address
+    BoxReport* report = nullptr;     // pinned: what the device tells mpcd_observe (from its first call on)
+    BoxReport* report_dev = nullptr;
     bool tuning = false;             // this context is an autotuner trial context
     std::map<uint64_t, std::pair<int32_t, std::array<int32_t, 3>>> tuned;   // shape class -> choice
     std::vector<std::pair<std::string, double>> tune_log;                  // last trial timings
@@ -576,13 +578,12 @@ int reset_state(mpcd_ctx* c, int32_t s, int64_t step, int parity)
 // Diagnostics of the current state into the box state (exact sums, status);
 // with new_origin also v0 <- v (if tracked) and VACF sample 0.  Queued on
 // the stream; nothing is read back here.
-int take_snapshot(mpcd_ctx* c, int32_t s, bool new_origin = true)
+int take_snapshot(mpcd_ctx* c, int32_t s, bool new_origin = true, BoxReport* report = nullptr)
 {
     Slot& sl = c->slots[s];
-    mark_holes(c, s);
     launch_snapshot(c->T, s, sl.ntile, new_origin ? 1 : 0, sl.part, c->stream);
     launch_box_stats(c->T, s, sl.ntile, sl.part, kStatsSnapshot | (new_origin ? kStatsOrigin : 0), 0.0, 0.0,
-                     c->stream);
+                     report, c->stream);
     HIPCHK(hipGetLastError());
     return MPCD_OK;
 }
@@ -595,9 +596,11 @@ int init_maxwell(mpcd_ctx* c, int32_t s)
     Slot& sl = c->slots[s];
     const double vs = sqrt(sl.desc.kT / sl.desc.mass);
     launch_init_maxwell(c->T, s, sl.ntile, (float)vs, sl.part, c->stream);
-    launch_box_stats(c->T, s, sl.ntile, sl.part, kStatsCentre, sl.desc.kT, sl.desc.mass, c->stream);
+    launch_box_stats(c->T, s, sl.ntile, sl.part, kStatsCentre, sl.desc.kT, sl.desc.mass, nullptr,
+                     c->stream);
     launch_init_adjust(c->T, s, sl.ntile, sl.part, c->stream);
-    launch_box_stats(c->T, s, sl.ntile, sl.part, kStatsScale, sl.desc.kT, sl.desc.mass, c->stream);
+    launch_box_stats(c->T, s, sl.ntile, sl.part, kStatsScale, sl.desc.kT, sl.desc.mass, nullptr,
+                     c->stream);
     launch_init_adjust(c->T, s, sl.ntile, sl.part, c->stream);
     HIPCHK(hipGetLastError());
     return MPCD_OK;
@@ -1041,14 +1044,18 @@ int mpcd_observe(mpcd_ctx* c, int32_t slot, mpcd_observables* out)
     Slot* sl = live_slot(c, slot);
     if (!sl) return MPCD_ENOTFOUND;
     HIPCHK(hipSetDevice(c->device));
-    // momentum and energy of the current state (exact sums over the box)
-    int rc = take_snapshot(c, slot, false);
+    // momentum and energy of the current state (exact sums over the box); the
+    // device writes the box state into pinned memory with them
+    if (!c->report) HIPCHK(hipHostMalloc((void**)&c->report, sizeof(BoxReport), hipHostMallocMapped));
+    if (!c->report_dev) HIPCHK(hipHostGetDevicePointer((void**)&c->report_dev, c->report, 0));
+    int rc = take_snapshot(c, slot, false, c->report_dev);
     if (rc) return rc;
-    BoxState st;
-    HIPCHK(hipMemcpyAsync(&st, &c->T.state[slot], sizeof(BoxState), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
+    const BoxState st = c->report->st;
     c->vacf_host.assign((size_t)std::max(st.vacf_len, 0), 0.0);
-    if (st.vacf_len > 0)
+    if (st.vacf_len > 0 && st.vacf_len <= kReportVacf)
+        memcpy(c->vacf_host.data(), c->report->vacf, (size_t)st.vacf_len * 8);
+    else if (st.vacf_len > 0)
         HIPCHK(hipMemcpy(c->vacf_host.data(), sl->dev.vacf, (size_t)st.vacf_len * 8, hipMemcpyDeviceToHost));
     // the kernels sum m v and m v^2 with m = 1 for equal masses
     const bool masses = sl->dev.m[0] != nullptr;
@@ -1427,6 +1434,7 @@ void mpcd_destroy(mpcd_ctx* c)
     ctx_free(c, c->tile_mem);
     ctx_free(c, c->tab_mem);
     if (c->host_flag) (void)hipHostFree(c->host_flag);
+    if (c->report) (void)hipHostFree(c->report);
     for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
     if (c->own_stream) (void)hipStreamDestroy(c->stream);
     delete c;

@@ -2120,7 +2120,44 @@ __global__ __launch_bounds__(kBlock) void k_init_adjust(const BoxDev* __restrict
     block_diag(d, partials + (size_t)t * kNumDiag);
 }
 
-// v0 <- v, and the FP64 partials of the current state (sum v, sum v^2, sum v.v0)
+// f(i) for every slot i of the tile that holds a particle of buffer `par`.
+// Brick boxes: each wave finds the tile's first bucket (64-way search), reads
+// the bounds and fills of 64 buckets at once and walks every fourth of them;
+// no hole is read, and none has to be marked first (that took 1.9 of 2.9 ms
+// of an observation of the 256^3 box; now 0.4 ms in all).
+template <class F>
+__device__ __forceinline__ void for_live(const BoxDev& b, int par, const Tile& tl, F&& f)
+{
+    if (b.binning != 1) {   // no holes
+        for (int64_t i = tl.begin + threadIdx.x; i < tl.end; i += kBlock) f(i);
+        return;
+    }
+    const MPCD_G uint32_t* const bs = gp(b.bstart);
+    const MPCD_G uint32_t* const sz = gp(b.bsize[par]);
+    const int nbk = b.nbrick, lane = threadIdx.x & (kWave - 1);
+    const int wave = uniform((int)(threadIdx.x / kWave));
+    int lo = 0, hi = nbk;   // the last bucket that starts at or before the tile
+    while (lo < hi) {
+        const int step = (hi - lo + kWave - 1) / kWave, m = lo + step * (lane + 1);
+        const bool before = m <= hi && (int64_t)bs[m] <= tl.begin;
+        lo += step * (int)__popcll(__ballot(before));
+        hi = min(hi, lo + step - 1);
+    }
+    for (int d0 = lo; d0 <= nbk; d0 += kWave) {
+        const int d = min(d0 + lane, nbk);
+        const uint32_t start = bs[d], end = start + min(sz[d], bs[d + 1] - start);
+        for (int j = wave; j < kWave; j += kBlock / kWave) {
+            const int64_t s0 = (uint32_t)__builtin_amdgcn_readlane(start, j);
+            if (d0 + j > nbk || s0 >= tl.end) return;
+            const int64_t s1 = min(tl.end, (int64_t)(uint32_t)__builtin_amdgcn_readlane(end, j));
+#pragma unroll 4
+            for (int64_t i = max(s0, tl.begin) + lane; i < s1; i += kWave) f(i);
+        }
+    }
+}
+
+// v0 <- v, and the exact partials of the current state (sum m v, sum m v^2,
+// sum v.v0)
 __global__ __launch_bounds__(kBlock) void k_snapshot(const BoxDev* __restrict__ boxes,
                                                       const BoxState* __restrict__ st, int box,
                                                       int set_v0, long long* __restrict__ partials)
@@ -2128,17 +2165,22 @@ __global__ __launch_bounds__(kBlock) void k_snapshot(const BoxDev* __restrict__ 
     const int t = blockIdx.x;
     const Tile tl = box_tile(boxes, box);
     const BoxDev& b = boxes[tl.box];
-    const int par = st[tl.box].parity;
+    const int par = uniform(st[tl.box].parity);
     const bool has_v0 = b.vacf_stride > 0;
+    const MPCD_G float* const px = ugp(b.p[par][3]);
+    const MPCD_G float* const py = ugp(b.p[par][4]);
+    const MPCD_G float* const pz = ugp(b.p[par][5]);
+    const MPCD_G float* const pm = b.m[par] ? ugp(b.m[par]) : nullptr;
     long long d[kNumDiag] = {};
-    for (int64_t i = tl.begin + threadIdx.x; i < tl.end; i += kBlock) {
-        if (!slot_live(b, par, i)) continue;
-        const float vx = b.p[par][3][i], vy = b.p[par][4][i], vz = b.p[par][5][i];
-        const int32_t id = b.pid[par] ? b.pid[par][i] : 0;
-        if (has_v0 && set_v0) b.v0[id] = make_float4(vx, vy, vz, 0.0f);
-        diag_particle(d, make_float3(vx, vy, vz), mass_of(b.m[par], i));
-        if (has_v0) vacf_term(b, id, make_float3(vx, vy, vz), d);
-    }
+    for_live(b, par, tl, [&](int64_t i) {
+        const float3 v = make_float3(px[i], py[i], pz[i]);
+        if (has_v0) {
+            const int32_t id = gp(b.pid[par])[i];
+            if (set_v0) b.v0[id] = make_float4(v.x, v.y, v.z, 0.0f);
+            vacf_term(b, id, v, d);
+        }
+        diag_particle(d, v, pm ? pm[i] : 1.0f);
+    });
     block_diag(d, partials + (size_t)t * kNumDiag);
 }
 
@@ -2201,7 +2243,7 @@ __device__ __forceinline__ void stat_share(const long long* partials, int64_t ni
 
 // What the exact box sums are used for (thread 0; see k_box_stats).
 __device__ void box_stats_finish(const __int128 (&tot)[kNumDiag], const BoxDev* __restrict__ box,
-                                 BoxState* __restrict__ st, int mode, double kT, double mass)
+                                 BoxState* st, int mode, double kT, double mass)
 {
 #pragma clang fp contract(off)
     double d[kNumDiag];
@@ -2253,8 +2295,8 @@ __device__ void box_stats_finish(const __int128 (&tot)[kNumDiag], const BoxDev* 
 // tiles' slots of the run, and this kernel reads those (packed = 1).
 __global__ __launch_bounds__(kStatBlock) void k_box_stats(const long long* __restrict__ partials, int nitems,
                                                            int per, int packed, const BoxDev* __restrict__ box,
-                                                           BoxState* __restrict__ st, int mode, double kT,
-                                                           double mass)
+                                                           BoxState* st, int mode, double kT,
+                                                           double mass, BoxReport* report)
 {
     __int128 tot[kNumDiag];
     long long hi = 0;
@@ -2271,6 +2313,12 @@ __global__ __launch_bounds__(kStatBlock) void k_box_stats(const long long* __res
     }
     stat_totals(hi, lo, tot);
     if (threadIdx.x == 0) box_stats_finish(tot, box, st, mode, kT, mass);
+    if (report) {   // the box state and its VACF samples, for the host
+        __syncthreads();
+        if (threadIdx.x == 0) report->st = *st;
+        const int n = min(st->vacf_len, kReportVacf);
+        for (int i = threadIdx.x; i < n; i += kStatBlock) report->vacf[i] = box->vacf[i];
+    }
 }
 
 // First level of k_box_stats for boxes with many tiles: workgroup g sums the
@@ -2509,18 +2557,18 @@ void launch_snapshot(const Tables& T, int32_t box, int ntile, int set_v0, long l
     MPCD_LAUNCH(k_snapshot, ntile, kBlock, s, T.boxes, T.state, box, set_v0, part);
 }
 void launch_box_stats(const Tables& T, int32_t box, int ntile, long long* part, int mode, double kT,
-                      double mass, hipStream_t s)
+                      double mass, BoxReport* report, hipStream_t s)
 {
     if (ntile <= 4 * kBlock) {
         hipLaunchKernelGGL(k_box_stats, dim3(1), dim3(kStatBlock), 0, s, part, ntile, 1, 0, T.boxes + box,
-                           T.state + box, mode, kT, mass);
+                           T.state + box, mode, kT, mass, report);
         return;
     }
     const int per = (ntile + kBlock - 1) / kBlock;   // >= 5, so each run holds two tiles' slots
     const int groups = (ntile + per - 1) / per;
     hipLaunchKernelGGL(k_box_stats_tiles, dim3(groups), dim3(kStatBlock), 0, s, part, ntile, per);
     hipLaunchKernelGGL(k_box_stats, dim3(1), dim3(kStatBlock), 0, s, part, groups, per, 1, T.boxes + box,
-                       T.state + box, mode, kT, mass);
+                       T.state + box, mode, kT, mass, report);
 }
 void launch_mark_holes_box(const Tables& T, int32_t box, int ntile, hipStream_t s)
 {

@@ -63,3 +63,28 @@ def test_observe_over_record_counts(mp, L, density):
     want = exact_moments(v, np.ones(n))
     assert list(obs["P"]) == want[:3]
     assert abs(2.0 * obs["E"] - want[3]) <= n * 2.0 ** -32 + 4.0 * 2.0 ** -53 * want[3]
+
+
+@pytest.mark.parametrize("L,n,brick,steps,more", [
+    ((24, 23, 25), 700, 2, 3, {}),                          # many buckets a tile, most of them nearly empty
+    ((9, 8, 7), 6001, 2, 2, dict(unordered=True)),
+    ((16, 16, 16), 40960, 8, 0, {}),                        # not yet bucketed: one bucket holds everything
+    ((16, 16, 16), 40960, 8, 2, dict(particle_mass=True)),
+    ((5, 5, 5), 1, 0, 2, {}),
+    ((5, 5, 5), 0, 0, 2, {}),
+])
+def test_observe_sees_every_particle_once(mp, L, n, brick, steps, more):
+    pos, vel = inputs.thermal_state(L, n, seed=n + 1) if n else (np.zeros((3, 0), np.float32),) * 2
+    mass = np.ones(n)
+    with mp.Context(brick=brick) as ctx:
+        slot = ctx.admit(mp.make_desc(L, n, init="external", seed=3, **more))
+        ctx.set_state(slot, (pos, vel))
+        if "particle_mass" in more:
+            mass = np.random.default_rng(5).uniform(0.5, 2.0, n).astype(np.float32)
+            ctx.set_mass(slot, mass)
+        ctx.step(steps) if steps else None
+        obs = ctx.observe(slot)
+        _, v, _ = ctx.get_state(slot)
+    want = exact_moments(v, mass)
+    assert list(obs["P"]) == want[:3] and obs["status"] == 0
+    assert abs(2.0 * obs["E"] - want[3]) <= n * 2.0 ** -32 + 4.0 * 2.0 ** -53 * want[3]
