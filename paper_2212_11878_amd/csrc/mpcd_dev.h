@@ -147,11 +147,12 @@ struct BoxState {
     float adj[4];          // initial-state adjustment v <- (v - adj[0..2]) * adj[3]
 };
 
-// What mpcd_observe reads, written by the device into pinned host memory: the
+// What mpcd_observe and the state transfers read, written by the device into pinned host memory: the
 // box state and its first kReportVacf VACF samples.
 constexpr int kReportVacf = 4096;
 struct BoxReport {
     BoxState st;
+    long long count;       // k_state_report: particles with a valid id; k_state_load: 1 for a bad value
     double vacf[kReportVacf];
 };
 

@@ -85,6 +85,7 @@ struct mpcd_ctx {
     int* host_flag_dev = nullptr;    // its device address
     BoxReport* report = nullptr;     // pinned: what the device tells mpcd_observe (from its first call on)
     BoxReport* report_dev = nullptr;
+    float* state_stage = nullptr;    // pinned, kStageBytes: small states on their way (from the first on)
     bool tuning = false;             // this context is an autotuner trial context
     std::map<uint64_t, std::pair<int32_t, std::array<int32_t, 3>>> tuned;   // shape class -> choice
     std::vector<std::pair<std::string, double>> tune_log;                  // last trial timings
@@ -575,6 +576,28 @@ int reset_state(mpcd_ctx* c, int32_t s, int64_t step, int parity)
     return upload(c, &c->T.state[s], &st, sizeof(BoxState));
 }
 
+// The pinned report (from its first use on).
+int need_report(mpcd_ctx* c)
+{
+    if (!c->report) HIPCHK(hipHostMalloc((void**)&c->report, sizeof(BoxReport), hipHostMallocMapped));
+    if (!c->report_dev) HIPCHK(hipHostGetDevicePointer((void**)&c->report_dev, c->report, 0));
+    return MPCD_OK;
+}
+
+// Pinned staging of states up to kStageBytes: the device reads or writes it in
+// place, which saves the runtime's copies (a fixed cost of tens of
+// microseconds); larger states are copied to and from the caller's memory.
+constexpr size_t kStageBytes = 1 << 20;
+float* state_stage(mpcd_ctx* c, int64_t n, float** dev)
+{
+    *dev = nullptr;
+    if ((size_t)n * 24 > kStageBytes) return nullptr;
+    if (!c->state_stage && hipHostMalloc((void**)&c->state_stage, kStageBytes, hipHostMallocMapped) != hipSuccess)
+        c->state_stage = nullptr;
+    if (!c->state_stage || hipHostGetDevicePointer((void**)dev, c->state_stage, 0) != hipSuccess) return nullptr;
+    return c->state_stage;
+}
+
 // Diagnostics of the current state into the box state (exact sums, status);
 // with new_origin also v0 <- v (if tracked) and VACF sample 0.  Queued on
 // the stream; nothing is read back here.
@@ -1046,9 +1069,8 @@ int mpcd_observe(mpcd_ctx* c, int32_t slot, mpcd_observables* out)
     HIPCHK(hipSetDevice(c->device));
     // momentum and energy of the current state (exact sums over the box); the
     // device writes the box state into pinned memory with them
-    if (!c->report) HIPCHK(hipHostMalloc((void**)&c->report, sizeof(BoxReport), hipHostMallocMapped));
-    if (!c->report_dev) HIPCHK(hipHostGetDevicePointer((void**)&c->report_dev, c->report, 0));
-    int rc = take_snapshot(c, slot, false, c->report_dev);
+    int rc = need_report(c);
+    if (!rc) rc = take_snapshot(c, slot, false, c->report_dev);
     if (rc) return rc;
     HIPCHK(hipStreamSynchronize(c->stream));
     const BoxState st = c->report->st;
@@ -1088,32 +1110,31 @@ int mpcd_get_state(mpcd_ctx* c, int32_t slot, float* xyzv, int64_t* step)
     if (!c || !xyzv) return MPCD_EINVAL;
     if (!sl) return MPCD_ENOTFOUND;
     HIPCHK(hipSetDevice(c->device));
+    const int64_t n = sl->dev.n, ns = sl->dev.nslot;
+    if (n > 0 && sl->dev.pid[0]) {   // particle-id order, put together on the device
+        int rc = need_report(c);
+        if (rc) return rc;
+        float* stage_dev = nullptr;
+        const float* const stage = state_stage(c, n, &stage_dev);
+        launch_state_by_id(c->T, slot, sl->ntile, n, sl->part, c->report_dev, stage_dev, c->stream);
+        HIPCHK(hipGetLastError());
+        HIPCHK(hipStreamSynchronize(c->stream));
+        const BoxState& st = c->report->st;
+        if (c->report->count != n) return MPCD_ESTATE;
+        if (stage)
+            memcpy(xyzv, stage, (size_t)n * 24);
+        else
+            HIPCHK(hipMemcpy(xyzv, sl->dev.p[st.parity ^ 1][0], (size_t)n * 24, hipMemcpyDeviceToHost));
+        if (step) *step = st.k;
+        return MPCD_OK;
+    }
     BoxState st;
     HIPCHK(hipMemcpyAsync(&st, &c->T.state[slot], sizeof(BoxState), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
-    const int64_t n = sl->dev.n, ns = sl->dev.nslot;
     mark_holes(c, slot);
     HIPCHK(hipStreamSynchronize(c->stream));
     c->stage.resize((size_t)ns);
-    c->stage_pid.resize((size_t)ns);
-    if (n > 0 && sl->dev.pid[st.parity]) {   // particle-id order
-        HIPCHK(hipMemcpy(c->stage_pid.data(), sl->dev.pid[st.parity], (size_t)ns * 4, hipMemcpyDeviceToHost));
-        int64_t seen = 0;
-        for (int64_t i = 0; i < ns; ++i) {
-            const int32_t id = c->stage_pid[i];
-            if (id >= n) return MPCD_ESTATE;
-            seen += id >= 0;
-        }
-        if (seen != n) return MPCD_ESTATE;
-        for (int d = 0; d < 6; ++d) {
-            HIPCHK(hipMemcpy(c->stage.data(), sl->dev.p[st.parity][d], (size_t)ns * 4, hipMemcpyDeviceToHost));
-            float* dst = xyzv + (size_t)d * n;
-            for (int64_t i = 0; i < ns; ++i) {
-                const int32_t id = c->stage_pid[i];
-                if (id >= 0) dst[id] = c->stage[i];
-            }
-        }
-    } else if (n > 0) {   // no ids: storage order, holes (x = -1) left out
+    if (n > 0) {   // no ids: storage order, holes (x = -1) left out
         std::vector<int64_t> live;
         live.reserve((size_t)n);
         HIPCHK(hipMemcpy(c->stage.data(), sl->dev.p[st.parity][0], (size_t)ns * 4, hipMemcpyDeviceToHost));
@@ -1137,37 +1158,37 @@ int mpcd_set_state(mpcd_ctx* c, int32_t slot, const float* xyzv, int64_t step)
     if (!c || !xyzv || step < 0) return MPCD_EINVAL;
     if (!sl) return MPCD_ENOTFOUND;
     const int64_t n = sl->dev.n;
-    for (int d = 0; d < 3; ++d) {
-        const float len = sl->dev.len[d];
-        const float* p = xyzv + (size_t)d * n;
-        for (int64_t i = 0; i < n; ++i)
-            if (!(p[i] >= 0.0f && p[i] < len)) return MPCD_EINVAL;
-    }
-    for (int64_t i = 3 * n; i < 6 * n; ++i)
-        if (!isfinite(xyzv[i])) return MPCD_EINVAL;
     HIPCHK(hipSetDevice(c->device));
+    int rc = need_report(c);
+    if (rc) return rc;
+    BoxState st;
+    HIPCHK(hipMemcpyAsync(&st, &c->T.state[slot], sizeof(BoxState), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
-    if (n > 0 && sl->dev.m[0]) {   // masses back into particle-id order, in buffer 0
-        BoxState st;
-        HIPCHK(hipMemcpy(&st, &c->T.state[slot], sizeof(BoxState), hipMemcpyDeviceToHost));
-        const int par = st.parity;
-        mark_holes(c, slot);
-        launch_permute_f32(sl->dev.m[par ^ 1], sl->dev.m[par], sl->dev.pid[par], sl->dev.nslot, n, 1, c->stream);
-        if (par == 0)
-            HIPCHK(hipMemcpyAsync(sl->dev.m[0], sl->dev.m[1], (size_t)n * 4, hipMemcpyDeviceToDevice, c->stream));
-        HIPCHK(hipStreamSynchronize(c->stream));
-    }
+    // the new state goes to the idle buffer, is checked there, and only then
+    // becomes the current one
+    const int par = st.parity, to = par ^ 1;
     if (n > 0) {
-        for (int d = 0; d < 6; ++d)
-            HIPCHK(hipMemcpy(sl->dev.p[0][d], xyzv + (size_t)d * n, (size_t)n * 4, hipMemcpyHostToDevice));
-        if (sl->dev.pid[0]) launch_fill_iota(sl->dev.pid[0], n, c->stream);
+        c->report->count = 0;
+        float* stage_dev = nullptr;
+        float* const stage = state_stage(c, n, &stage_dev);
+        if (stage)
+            memcpy(stage, xyzv, (size_t)n * 24);
+        else
+            for (int d = 0; d < 6; ++d)
+                HIPCHK(hipMemcpy(sl->dev.p[to][d], xyzv + (size_t)d * n, (size_t)n * 4, hipMemcpyHostToDevice));
+        launch_state_load(c->T, slot, to, n, stage_dev, c->report_dev, c->stream);
+        HIPCHK(hipGetLastError());
+        HIPCHK(hipStreamSynchronize(c->stream));
+        if (c->report->count) return MPCD_EINVAL;
+        if (sl->dev.m[0]) {   // masses back into particle-id order
+            mark_holes(c, slot);
+            launch_permute_f32(sl->dev.m[to], sl->dev.m[par], sl->dev.pid[par], sl->dev.nslot, n, 1, c->stream);
+        }
+        if (sl->dev.pid[0]) launch_fill_iota(sl->dev.pid[to], n, c->stream);
         HIPCHK(hipGetLastError());
     }
-    {
-        int rc = set_compact_layout(c, slot, 0);
-        if (rc) return rc;
-    }
-    int rc = reset_state(c, slot, step, 0);
+    rc = set_compact_layout(c, slot, to);
+    if (!rc) rc = reset_state(c, slot, step, to);
     if (rc) return rc;
     rc = take_snapshot(c, slot);
     if (rc) return rc;
@@ -1435,6 +1456,7 @@ void mpcd_destroy(mpcd_ctx* c)
     ctx_free(c, c->tab_mem);
     if (c->host_flag) (void)hipHostFree(c->host_flag);
     if (c->report) (void)hipHostFree(c->report);
+    if (c->state_stage) (void)hipHostFree(c->state_stage);
     for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
     if (c->own_stream) (void)hipStreamDestroy(c->stream);
     delete c;

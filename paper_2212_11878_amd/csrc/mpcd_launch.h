@@ -57,6 +57,14 @@ void launch_snapshot(const Tables& T, int32_t box, int ntile, int set_v0, long l
 enum { kStatsCentre = 0, kStatsScale = 1, kStatsSnapshot = 2, kStatsOrigin = 4 };
 void launch_box_stats(const Tables& T, int32_t box, int ntile, long long* part, int mode, double kT,
                       double mass, BoxReport* report, hipStream_t s);   // consumes the partials
+// a box's state in id order into its idle buffer, box state and count of valid
+// particles into `report`, and the state into `host` (pinned) if given
+void launch_state_by_id(const Tables& T, int32_t box, int ntile, int64_t n, long long* counts, BoxReport* report,
+                        float* host, hipStream_t s);
+// a new state of n particles in buffer `to` (from `host`, pinned, if given),
+// checked: report->count becomes 1 on a bad value
+void launch_state_load(const Tables& T, int32_t box, int to, int64_t n, const float* host, BoxReport* report,
+                       hipStream_t s);
 void launch_mark_holes_box(const Tables& T, int32_t box, int ntile, hipStream_t s);
 void launch_fill_iota(int32_t* p, int64_t n, hipStream_t s);
 void launch_fill_zero_u32(uint32_t* p, int64_t n, hipStream_t s);

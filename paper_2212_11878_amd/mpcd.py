@@ -437,7 +437,7 @@ class Context:
     def get_state(self, slot):
         rc, buf, step = mpcd_get_state(self.handle, slot, self.n[slot])
         _check(rc, "mpcd_get_state")
-        return buf[:3].copy(), buf[3:].copy(), step
+        return buf[:3], buf[3:], step
 
     def step(self, n=1):
         _check(mpcd_step(self.handle, n), "mpcd_step")

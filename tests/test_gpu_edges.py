@@ -88,3 +88,35 @@ def test_observe_sees_every_particle_once(mp, L, n, brick, steps, more):
     want = exact_moments(v, mass)
     assert list(obs["P"]) == want[:3] and obs["status"] == 0
     assert abs(2.0 * obs["E"] - want[3]) <= n * 2.0 ** -32 + 4.0 * 2.0 ** -53 * want[3]
+
+
+@pytest.mark.parametrize("n", [43690, 43691])   # the last state that fits the pinned staging, the first that does not
+@pytest.mark.parametrize("binning,more", [(1, {}), (2, {}), (1, dict(particle_mass=True))])
+def test_state_round_trip_at_the_staging_limit(mp, n, binning, more):
+    L = (17, 16, 16)
+    pos, vel = inputs.thermal_state(L, n, seed=n)
+    with mp.Context(binning=binning) as ctx:
+        slot = ctx.admit(mp.make_desc(L, n, init="external", seed=3, **more))
+        ctx.set_state(slot, (pos, vel), 7)
+        ctx.step(1)
+        p1, v1, step = ctx.get_state(slot)
+        assert step == 8
+        ctx.set_state(slot, (p1, v1), step)      # from either buffer
+        p2, v2, step = ctx.get_state(slot)
+        assert step == 8 and np.array_equal(p1, p2) and np.array_equal(v1, v2)
+        # a bad value anywhere is refused and changes nothing
+        for field, i, value in ((0, 0, -1.0), (2, n - 1, 16.0), (1, n // 2, np.nan), (3, n - 1, np.inf),
+                                (5, 0, np.nan)):
+            bad = np.concatenate([p1, v1])
+            bad[field, i] = value
+            with pytest.raises(mp.MPCDError) as e:
+                ctx.set_state(slot, (bad[:3], bad[3:]), 3)
+            assert e.value.status == mp.MPCD_EINVAL
+        p2, v2, step = ctx.get_state(slot)
+        assert step == 8 and np.array_equal(p1, p2) and np.array_equal(v1, v2)
+        ctx.step(1)
+        p3, v3, _ = ctx.get_state(slot)
+        ctx.set_state(slot, (p1, v1), 8)
+        ctx.step(1)
+        p4, v4, _ = ctx.get_state(slot)
+        assert np.array_equal(p3, p4) and np.array_equal(v3, v4)
