@@ -38,6 +38,19 @@ const char* const kKernName[K_NUM] = {
     "mark_holes", "zero_counts", "count", "scan", "scatter", "flip", "brick_step", "cell_rotate",
     "box_finish"};
 
+// Steps of one captured graph; what a call asks for beyond multiples of it is
+// launched eagerly.  Replaying a graph costs about 16 us of host time and 6 us
+// between graphs whatever it holds: with one step in it an 8^3..32^3 box took
+// 19 to 22 us a step, with 16 steps (or launched eagerly, at 7 us of host time
+// a step) 14 to 18; 32 steps gain less than 1 % more.
+constexpr int kGraphSteps = 16;
+
+// Short calls (fewer than kGraphSteps steps) that may be queued at once.
+// Launched eagerly they cost the host less time than the GPU, and a host that
+// ran ahead without bound would learn of a full bucket (host_flag) only after
+// all it had queued.
+constexpr int kShortCalls = 4;
+
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 struct Slot {
@@ -83,9 +96,10 @@ struct mpcd_ctx {
     bool pending_rebucket = false;
     int* host_flag = nullptr;        // pinned: set by the device when a brick box needs re-bucketing
     int* host_flag_dev = nullptr;    // its device address
-    BoxReport* report = nullptr;     // pinned: what the device tells mpcd_observe (from its first call on)
+    BoxReport* report = nullptr;     // pinned: what the device tells the calls that read a box (with host_flag)
     BoxReport* report_dev = nullptr;
-    float* state_stage = nullptr;    // pinned, kStageBytes: small states on their way (from the first on)
+    float* state_stage = nullptr;    // pinned, at most kStageBytes: small states on their way (from the first on)
+    size_t stage_cap = 0;
     bool tuning = false;             // this context is an autotuner trial context
     std::map<uint64_t, std::pair<int32_t, std::array<int32_t, 3>>> tuned;   // shape class -> choice
     std::vector<std::pair<std::string, double>> tune_log;                  // last trial timings
@@ -105,6 +119,11 @@ struct mpcd_ctx {
     hipGraph_t graph = nullptr;
     hipGraphExec_t graph_exec = nullptr;
     std::vector<Retired> retired;
+
+    // calls of fewer than kGraphSteps steps since the host last waited for the
+    // stream, and an event behind each but the first of the last kShortCalls
+    int64_t short_calls = 0;
+    hipEvent_t short_done[kShortCalls] = {};
 
     // host-to-device uploads are stream-ordered through pinned staging
     std::vector<Upload> uploads;
@@ -506,7 +525,8 @@ int capture_graph(mpcd_ctx* c)
     int rc0 = drop_graph(c);
     if (rc0) return rc0;
     HIPCHK(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-    int rc = enqueue_step(c, false);
+    int rc = MPCD_OK;
+    for (int i = 0; i < kGraphSteps && !rc; ++i) rc = enqueue_step(c, false);
     hipGraph_t g = nullptr;
     hipError_t e = hipStreamEndCapture(c->stream, &g);
     if (rc) {
@@ -576,14 +596,6 @@ int reset_state(mpcd_ctx* c, int32_t s, int64_t step, int parity)
     return upload(c, &c->T.state[s], &st, sizeof(BoxState));
 }
 
-// The pinned report (from its first use on).
-int need_report(mpcd_ctx* c)
-{
-    if (!c->report) HIPCHK(hipHostMalloc((void**)&c->report, sizeof(BoxReport), hipHostMallocMapped));
-    if (!c->report_dev) HIPCHK(hipHostGetDevicePointer((void**)&c->report_dev, c->report, 0));
-    return MPCD_OK;
-}
-
 // Pinned staging of states up to kStageBytes: the device reads or writes it in
 // place, which saves the runtime's copies (a fixed cost of tens of
 // microseconds); larger states are copied to and from the caller's memory.
@@ -592,8 +604,14 @@ float* state_stage(mpcd_ctx* c, int64_t n, float** dev)
 {
     *dev = nullptr;
     if ((size_t)n * 24 > kStageBytes) return nullptr;
-    if (!c->state_stage && hipHostMalloc((void**)&c->state_stage, kStageBytes, hipHostMallocMapped) != hipSuccess)
-        c->state_stage = nullptr;
+    if (c->stage_cap < (size_t)n * 24) {   // no call is using it: each waits for its kernels
+        if (c->state_stage) (void)hipHostFree(c->state_stage);
+        c->stage_cap = 0;
+        if (hipHostMalloc((void**)&c->state_stage, (size_t)n * 24, hipHostMallocMapped) != hipSuccess)
+            c->state_stage = nullptr;
+        else
+            c->stage_cap = (size_t)n * 24;
+    }
     if (!c->state_stage || hipHostGetDevicePointer((void**)dev, c->state_stage, 0) != hipSuccess) return nullptr;
     return c->state_stage;
 }
@@ -861,14 +879,16 @@ int mpcd_create(const mpcd_options* opt, mpcd_ctx** out)
         delete c;
         return MPCD_ENOMEM;
     }
-    if (hipHostMalloc((void**)&c->host_flag, sizeof(int), hipHostMallocMapped) != hipSuccess ||
-        hipHostGetDevicePointer((void**)&c->host_flag_dev, c->host_flag, 0) != hipSuccess) {
-        if (c->host_flag) (void)hipHostFree(c->host_flag);
+    if (hipHostMalloc((void**)&c->report, sizeof(BoxReport) + sizeof(int), hipHostMallocMapped) != hipSuccess ||
+        hipHostGetDevicePointer((void**)&c->report_dev, c->report, 0) != hipSuccess) {
+        if (c->report) (void)hipHostFree(c->report);
         ctx_free(c, c->tab_mem);
         if (c->own_stream) (void)hipStreamDestroy(c->stream);
         delete c;
         return MPCD_EDEVICE;
     }
+    c->host_flag = (int*)(c->report + 1);
+    c->host_flag_dev = (int*)(c->report_dev + 1);
     *c->host_flag = 0;
     c->T.boxes = (BoxDev*)c->tab_mem;
     c->T.state = (BoxState*)((char*)c->tab_mem + align256(sizeof(BoxDev) * c->max_slots));
@@ -876,7 +896,7 @@ int mpcd_create(const mpcd_options* opt, mpcd_ctx** out)
     if (hipMemset(c->T.dacc, 0, sizeof(long long) * kAccLanes * 3 * c->max_slots) != hipSuccess) {
         ctx_free(c, c->tab_mem);
         if (c->own_stream) (void)hipStreamDestroy(c->stream);
-        (void)hipHostFree(c->host_flag);
+        (void)hipHostFree(c->report);
         delete c;
         return MPCD_EDEVICE;
     }
@@ -1032,6 +1052,9 @@ int mpcd_step(mpcd_ctx* c, int32_t n)
         if (rc) return rc;
     }
     if (c->T.nactive == 0) return MPCD_OK;
+    const bool bounded = c->use_graph && !c->profiling && n < kGraphSteps;
+    if (bounded && c->short_calls >= kShortCalls)
+        HIPCHK(hipEventSynchronize(c->short_done[std::max<int64_t>(c->short_calls - kShortCalls, 1) % kShortCalls]));
     // a bucket overflowed in an earlier step: the boxes concerned carry the
     // rebucket flag; re-bucket them in the next step
     if (__atomic_exchange_n(c->host_flag, 0, __ATOMIC_ACQ_REL) != 0) c->pending_rebucket = true;
@@ -1039,24 +1062,32 @@ int mpcd_step(mpcd_ctx* c, int32_t n)
         int rc = enqueue_step(c, true);
         if (rc) return rc;
         c->pending_rebucket = false;
-        if (--n == 0) return MPCD_OK;
+        --n;
     }
-    const bool graph = c->use_graph && !c->profiling;
-    if (graph && !c->graph_exec) {
-        int rc = capture_graph(c);
-        if (rc) return rc;
-    }
-    for (int i = 0; i < n; ++i) {
-        if (graph) {
-            HIPCHK(hipGraphLaunch(c->graph_exec, c->stream));
-        } else {
-            int rc = enqueue_step(c, false);
-            if (rc) return rc;
-            if (c->pending.size() > 4096) {
-                rc = harvest(c);
+    if (c->use_graph && !c->profiling) {
+        for (; n >= kGraphSteps; n -= kGraphSteps) {
+            if (!c->graph_exec) {
+                int rc = capture_graph(c);
                 if (rc) return rc;
             }
+            HIPCHK(hipGraphLaunch(c->graph_exec, c->stream));
         }
+    }
+    for (; n > 0; --n) {
+        int rc = enqueue_step(c, false);
+        if (rc) return rc;
+        if (c->pending.size() > 4096) {
+            rc = harvest(c);
+            if (rc) return rc;
+        }
+    }
+    if (bounded) {
+        if (c->short_calls > 0) {   // a step or two between calls that read the box leave no event
+            hipEvent_t& e = c->short_done[c->short_calls % kShortCalls];
+            if (!e) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+            HIPCHK(hipEventRecord(e, c->stream));
+        }
+        ++c->short_calls;
     }
     return MPCD_OK;
 }
@@ -1069,10 +1100,10 @@ int mpcd_observe(mpcd_ctx* c, int32_t slot, mpcd_observables* out)
     HIPCHK(hipSetDevice(c->device));
     // momentum and energy of the current state (exact sums over the box); the
     // device writes the box state into pinned memory with them
-    int rc = need_report(c);
-    if (!rc) rc = take_snapshot(c, slot, false, c->report_dev);
+    int rc = take_snapshot(c, slot, false, c->report_dev);
     if (rc) return rc;
     HIPCHK(hipStreamSynchronize(c->stream));
+    c->short_calls = 0;
     const BoxState st = c->report->st;
     c->vacf_host.assign((size_t)std::max(st.vacf_len, 0), 0.0);
     if (st.vacf_len > 0 && st.vacf_len <= kReportVacf)
@@ -1112,13 +1143,12 @@ int mpcd_get_state(mpcd_ctx* c, int32_t slot, float* xyzv, int64_t* step)
     HIPCHK(hipSetDevice(c->device));
     const int64_t n = sl->dev.n, ns = sl->dev.nslot;
     if (n > 0 && sl->dev.pid[0]) {   // particle-id order, put together on the device
-        int rc = need_report(c);
-        if (rc) return rc;
         float* stage_dev = nullptr;
         const float* const stage = state_stage(c, n, &stage_dev);
         launch_state_by_id(c->T, slot, sl->ntile, n, sl->part, c->report_dev, stage_dev, c->stream);
         HIPCHK(hipGetLastError());
         HIPCHK(hipStreamSynchronize(c->stream));
+        c->short_calls = 0;
         const BoxState& st = c->report->st;
         if (c->report->count != n) return MPCD_ESTATE;
         if (stage)
@@ -1159,8 +1189,6 @@ int mpcd_set_state(mpcd_ctx* c, int32_t slot, const float* xyzv, int64_t step)
     if (!sl) return MPCD_ENOTFOUND;
     const int64_t n = sl->dev.n;
     HIPCHK(hipSetDevice(c->device));
-    int rc = need_report(c);
-    if (rc) return rc;
     BoxState st;
     HIPCHK(hipMemcpyAsync(&st, &c->T.state[slot], sizeof(BoxState), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
@@ -1187,7 +1215,7 @@ int mpcd_set_state(mpcd_ctx* c, int32_t slot, const float* xyzv, int64_t step)
         if (sl->dev.pid[0]) launch_fill_iota(sl->dev.pid[to], n, c->stream);
         HIPCHK(hipGetLastError());
     }
-    rc = set_compact_layout(c, slot, to);
+    int rc = set_compact_layout(c, slot, to);
     if (!rc) rc = reset_state(c, slot, step, to);
     if (rc) return rc;
     rc = take_snapshot(c, slot);
@@ -1454,10 +1482,11 @@ void mpcd_destroy(mpcd_ctx* c)
         if (sl.live) ctx_free(c, sl.mem);
     ctx_free(c, c->tile_mem);
     ctx_free(c, c->tab_mem);
-    if (c->host_flag) (void)hipHostFree(c->host_flag);
     if (c->report) (void)hipHostFree(c->report);
     if (c->state_stage) (void)hipHostFree(c->state_stage);
     for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
+    for (hipEvent_t e : c->short_done)
+        if (e) (void)hipEventDestroy(e);
     if (c->own_stream) (void)hipStreamDestroy(c->stream);
     delete c;
 }

@@ -120,3 +120,24 @@ def test_state_round_trip_at_the_staging_limit(mp, n, binning, more):
         ctx.step(1)
         p4, v4, _ = ctx.get_state(slot)
         assert np.array_equal(p3, p4) and np.array_equal(v3, v4)
+
+
+@pytest.mark.parametrize("binning", [1, 2])
+def test_graph_blocks_and_single_steps(mp, binning):
+    """Calls of fewer steps than a graph holds, of whole graphs and of both,
+    with the host reading the box in between, against eager launches."""
+    L, n = (12, 11, 10), 13000
+    pos, vel = inputs.thermal_state(L, n, seed=8)
+    states = []
+    for graph in (True, False):
+        seen = []
+        with mp.Context(binning=binning, use_graph=graph) as ctx:
+            slot = ctx.admit(mp.make_desc(L, n, init="external", seed=3, vacf_stride=5))
+            ctx.set_state(slot, (pos, vel))
+            for steps in (1, 16, 15, 33, 48, 1, 64):
+                ctx.step(steps)
+                obs = ctx.observe(slot)
+                p, v, k = ctx.get_state(slot)
+                seen.append((obs["E"], tuple(obs["P"]), tuple(obs["vacf"]), k, p.tobytes(), v.tobytes()))
+        states.append(seen)
+    assert states[0] == states[1]
