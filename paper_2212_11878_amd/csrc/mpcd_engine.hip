@@ -415,7 +415,7 @@ int rebuild_tables(mpcd_ctx* c)
     c->T.brick_box = n_brick_boxes == 1 ? brick_box : -1;
     c->T.nactive = (int)active.size();
     c->T.max_bvol = max_bvol;
-    c->T.brick_shape = brick_shape_for(max_bucket);
+    c->T.brick_shape = brick_shape_for(max_bucket, (int)bt.size() <= kSmallGrid && !brick_am && !brick_wide);
     c->T.brick_mass = brick_mass;
     c->T.brick_am = brick_am;
     c->T.brick_wide = brick_wide;
@@ -746,7 +746,18 @@ static int autotune(mpcd_ctx* c, const mpcd_box_desc* d, int32_t* binning, int32
     const double C = (double)d->L[0] * d->L[1] * d->L[2];
     const double density = (double)d->n_particles / C;
     const bool am = (d->flags & MPCD_CONSERVE_L) != 0;
-    const int r = rule_shape(density, am);
+    int r = rule_shape(density, am);
+    // while every brick of the context has a CU of its own, smaller bricks
+    // shorten the step (more, shorter workgroups); boxes that join a larger
+    // batch keep the rule's, which cost less in all.  (Smaller bricks need more
+    // spare slots: not under a memory budget, which admits what it did.)
+    if (!c->tuning && c->budget == 0) {
+        int64_t live = 0;
+        for (const Slot& sl : c->slots)
+            if (sl.live) live += sl.dev.nbrick;
+        for (int i = 0; i < r; ++i)
+            if (rule_allowed(i, am) && live + brick_geometry(d->L, kRuleShapes[i]).nbrick <= kSmallGrid) r = i;
+    }
     // defaults, also used inside trial contexts, for empty and for small boxes
     *binning = MPCD_BIN_ATOMIC;
     for (int k = 0; k < 3; ++k) brick[k] = kRuleShapes[r][k];

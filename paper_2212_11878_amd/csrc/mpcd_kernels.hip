@@ -2558,28 +2558,47 @@ static void brick_step_at(const Tables& T, hipStream_t s)
     else brick_step_run<kT, kS, false, false, false>(T, s);
 }
 
+// Small grids: one instance for boxes with and without ids, one for masses.
+template <int kT, int kS>
+static void brick_step_small(const Tables& T, hipStream_t s)
+{
+    if (T.brick_mass) brick_step_run<kT, kS, true, false, true>(T, s);
+    else brick_step_run<kT, kS, false, false, true>(T, s);
+}
+
 // Launch shapes of the brick step (workgroup size, particles per thread),
 // smallest first: one workgroup holds threads x slots particles in
-// registers.  Small workgroups let many bricks per CU overlap their phases.
+// registers.  Large grids take few threads with many particles each, so that
+// many bricks per CU overlap their phases.  Grids of at most one brick per CU
+// (`small`) have nothing to overlap and their step lasts as long as one
+// workgroup: few particles per thread (and, where a box is alone, the smaller
+// bricks that mpcd_admit gives it).  Measured per step, ids, density 10: 10^3
+// cells 16.2 -> 10.9 us, 16^3 16.6 -> 10.6, 24^3 17.0 -> 12.9, 32^3 17.9 ->
+// 15.9; in a grid of 2048 bricks the small shapes are up to twice slower.
 static const struct {
     int threads, slots;
+    bool small;
     void (*run)(const Tables&, hipStream_t);
 } kBrickShapes[] = {
-    {128, 8, brick_step_at<128, 8>},
-    {256, 6, brick_step_at<256, 6>},   // fits 4 waves per SIMD
-    {256, 8, brick_step_at<256, 8>},
-    {512, 8, brick_step_at<512, 8>},
+    {256, 1, true, brick_step_small<256, 1>},
+    {512, 1, true, brick_step_small<512, 1>},
+    {512, 2, true, brick_step_small<512, 2>},
+    {512, 3, true, brick_step_small<512, 3>},
+    {1024, 2, true, brick_step_small<1024, 2>},
+    {128, 8, false, brick_step_at<128, 8>},
+    {256, 6, false, brick_step_at<256, 6>},
+    {256, 8, false, brick_step_at<256, 8>},
+    {512, 8, false, brick_step_at<512, 8>},
 };
 constexpr int kNumBrickShapes = (int)(sizeof(kBrickShapes) / sizeof(kBrickShapes[0]));
 
-int brick_shape_for(int64_t bucket)
+int brick_shape_for(int64_t bucket, bool small)
 {
     for (int i = 0; i < kNumBrickShapes; ++i)
-        if ((int64_t)kBrickShapes[i].threads * kBrickShapes[i].slots >= bucket) return i;
+        if ((small || !kBrickShapes[i].small) && (int64_t)kBrickShapes[i].threads * kBrickShapes[i].slots >= bucket)
+            return i;
     return kNumBrickShapes - 1;   // larger buckets run in several chunks
 }
-int brick_shape_threads(int shape) { return kBrickShapes[shape].threads; }
-int brick_shape_slots(int shape) { return kBrickShapes[shape].slots; }
 
 void launch_brick_step(const Tables& T, hipStream_t s)
 {

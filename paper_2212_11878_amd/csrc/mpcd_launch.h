@@ -35,9 +35,10 @@ struct Tables {
 };
 
 void launch_brick_step(const Tables& T, hipStream_t s);
-int brick_shape_for(int64_t bucket);   // launch shape whose workgroup holds `bucket` particles
-int brick_shape_threads(int shape);
-int brick_shape_slots(int shape);
+// launch shape whose workgroup holds `bucket` particles; `small`: a grid of at
+// most kSmallGrid bricks of boxes with the plain rule and 32-bit offsets
+int brick_shape_for(int64_t bucket, bool small);
+constexpr int kSmallGrid = 256;   // bricks: one per CU
 void launch_mark_holes(const Tile* tiles, int ntiles, const Tables& T, int all, hipStream_t s);
 void launch_rebucket_clear(const Tables& T, hipStream_t s);
 void launch_box_finish(const Tables& T, hipStream_t s);

@@ -141,3 +141,48 @@ def test_graph_blocks_and_single_steps(mp, binning):
                 seen.append((obs["E"], tuple(obs["P"]), tuple(obs["vacf"]), k, p.tobytes(), v.tobytes()))
         states.append(seen)
     assert states[0] == states[1]
+
+
+@pytest.mark.parametrize("per_brick", [1, 180, 195, 400, 425, 880, 905, 1370, 1390, 1850, 1900])
+@pytest.mark.parametrize("more", [{}, dict(unordered=True), dict(particle_mass=True)])
+def test_small_grid_shapes_equal_sort(mp, per_brick, more):
+    """Brick loads on both sides of every launch shape's capacity (mean plus
+    four standard deviations: 256, 512, 1024, 1536, 2048), in a grid of eight
+    bricks: the bits of counting-sort binning."""
+    from gpu_util import same_particle_set
+    L, n = (8, 8, 8), 8 * per_brick
+    pos, vel = inputs.thermal_state(L, n, seed=n)
+    mass = np.random.default_rng(n).uniform(0.5, 2.0, n).astype(np.float32)
+    out = []
+    for binning in (mp.MPCD_BIN_ATOMIC, mp.MPCD_BIN_SORT):
+        with mp.Context(binning=binning, brick=4) as ctx:
+            slot = ctx.admit(mp.make_desc(L, n, init="external", seed=3, **more))
+            ctx.set_state(slot, (pos, vel))
+            if "particle_mass" in more:
+                ctx.set_mass(slot, mass)
+            ctx.step(20)
+            out.append(ctx.get_state(slot))
+    if "unordered" in more:
+        assert same_particle_set(out[0][0], out[0][1], out[1][0], out[1][1])
+    else:
+        assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+
+
+def test_small_bricks_only_while_they_fit(mp):
+    """A box alone gets bricks for one step's latency (at most one per CU);
+    boxes admitted to a filled batch, or under a memory budget, the density
+    rule's; all run to the same bits."""
+    L, n = (16, 16, 16), 40960
+    pos, vel = inputs.thermal_state(L, n, seed=2)
+    desc = mp.make_desc(L, n, init="external", seed=3)
+    with mp.Context() as ctx, mp.Context(hbm_budget=1 << 30) as tight:
+        slots = [ctx.admit(desc, (pos, vel)) for _ in range(2)]
+        slots_tight = [tight.admit(desc, (pos, vel))]
+        bricks = [int(np.prod(ctx.observe(s)["brick"])) for s in slots]
+        rule = int(np.prod(tight.observe(slots_tight[0])["brick"]))
+        assert bricks[0] < rule and 4096 // bricks[0] <= 256 and bricks[1] == rule
+        ctx.step(20)
+        tight.step(20)
+        a, b, c = ctx.get_state(slots[0]), ctx.get_state(slots[1]), tight.get_state(slots_tight[0])
+    for x in (b, c):
+        assert np.array_equal(a[0], x[0]) and np.array_equal(a[1], x[1])
