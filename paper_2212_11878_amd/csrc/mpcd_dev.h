@@ -41,8 +41,9 @@ constexpr int kUnWords = 12;         // 32-bit words per brick cell's data recor
 constexpr int kBrickCellBytes = 8 * kAccWords + 4 * kUnWords;   // LDS per brick cell
 // Angular-momentum-conserving collision on bricks: per cell 18 64-bit LDS
 // words (first the 13 moment sums, then u, r_c, n, Q / omega in FP64 and the
-// 3 angular-momentum sums), and at most kMaxAmBrickCells cells per brick.
-constexpr int kAmWords = 18;
+// 3 angular-momentum sums) and one more, as an odd stride spreads the cells
+// over all banks, and at most kMaxAmBrickCells cells per brick.
+constexpr int kAmWords = 19;
 constexpr int kAmCellBytes = 8 * kAmWords;
 constexpr int kMaxAmBrickCells = 512;
 constexpr int kAccLanes = 64;        // step accumulator lanes per box (spread the atomics)
@@ -730,28 +731,49 @@ __device__ __forceinline__ void am_moments(double mj, float vx, float vy, float 
     t[12] = fixed_term(mj * r[2] * r[2]);
 }
 
-// Cell data from the first-pass sums: mean velocity u, centre of mass rc,
+// The same terms 1 .. 12 for mass 1, as FP64 integers below 2^40 (a <= 16,
+// velocities below the limit), so that sums of fewer than kMaxCellCount terms
+// are exact.
+__device__ __forceinline__ void am_moments_exact(float vx, float vy, float vz, const double r[3], double t[kAmMoments])
+{
+#pragma clang fp contract(off)
+    constexpr double kQ = 4294967296.0;
+    const double q[3] = {r[0] * kQ, r[1] * kQ, r[2] * kQ};   // scaling by 2^32 is exact
+    t[1] = rint((double)vx * kQ);
+    t[2] = rint((double)vy * kQ);
+    t[3] = rint((double)vz * kQ);
+#pragma unroll
+    for (int e = 0; e < 3; ++e) t[4 + e] = rint(q[e]);
+    t[7] = rint(q[0] * r[0]);
+    t[8] = rint(q[0] * r[1]);
+    t[9] = rint(q[0] * r[2]);
+    t[10] = rint(q[1] * r[1]);
+    t[11] = rint(q[1] * r[2]);
+    t[12] = rint(q[2] * r[2]);
+}
+
+// Cell data from the first-pass sums (integers, as FP64): mean velocity u, centre of mass rc,
 // second moment Q (xx, xy, xz, yy, yz, zz) about rc, and the unit axis n of
 // canonical cell c at step k.
-__device__ __forceinline__ void am_cell(const BoxDev& b, long long k, uint32_t c, const long long s[kAmMoments],
+__device__ __forceinline__ void am_cell(const BoxDev& b, long long k, uint32_t c, const double s[kAmMoments],
                                         double u[3], double rc[3], double Q[6], double n[3])
 {
 #pragma clang fp contract(off)
-    const double M = fixed_to_double((unsigned long long)s[0]);
+    const double M = s[0];
 #pragma unroll
     for (int e = 0; e < 3; ++e) {
-        u[e] = fixed_to_double((unsigned long long)s[1 + e]) / M;
-        rc[e] = fixed_to_double((unsigned long long)s[4 + e]) / M;
+        u[e] = s[1 + e] / M;
+        rc[e] = s[4 + e] / M;
     }
     // sums are in units of 2^-32: Mt is the true mass; u and rc are ratios
     const double k2 = 2.3283064365386963e-10;
     const double Mt = M * k2;
-    Q[0] = fixed_to_double((unsigned long long)s[7]) * k2 - Mt * rc[0] * rc[0];
-    Q[1] = fixed_to_double((unsigned long long)s[8]) * k2 - Mt * rc[0] * rc[1];
-    Q[2] = fixed_to_double((unsigned long long)s[9]) * k2 - Mt * rc[0] * rc[2];
-    Q[3] = fixed_to_double((unsigned long long)s[10]) * k2 - Mt * rc[1] * rc[1];
-    Q[4] = fixed_to_double((unsigned long long)s[11]) * k2 - Mt * rc[1] * rc[2];
-    Q[5] = fixed_to_double((unsigned long long)s[12]) * k2 - Mt * rc[2] * rc[2];
+    Q[0] = s[7] * k2 - Mt * rc[0] * rc[0];
+    Q[1] = s[8] * k2 - Mt * rc[0] * rc[1];
+    Q[2] = s[9] * k2 - Mt * rc[0] * rc[2];
+    Q[3] = s[10] * k2 - Mt * rc[1] * rc[1];
+    Q[4] = s[11] * k2 - Mt * rc[1] * rc[2];
+    Q[5] = s[12] * k2 - Mt * rc[2] * rc[2];
     const float3 ax = cell_axis(b, k, c);
     const double nx = ax.x, ny = ax.y, nz = ax.z;
     const double inv = 1.0 / sqrt(nx * nx + ny * ny + nz * nz);
@@ -776,11 +798,19 @@ __device__ __forceinline__ bool am_dl(double mj, float vx, float vy, float vz, c
     rotate_w(n[0], n[1], n[2], ca, sa, w, rw);
     const double rp[3] = {r[0] - rc[0], r[1] - rc[1], r[2] - rc[2]};
     const double dw[3] = {rw[0] - w[0], rw[1] - w[1], rw[2] - w[2]};
-    t[0] = fixed_term(mj * (rp[1] * dw[2] - rp[2] * dw[1]));
-    t[1] = fixed_term(mj * (rp[2] * dw[0] - rp[0] * dw[2]));
-    t[2] = fixed_term(mj * (rp[0] * dw[1] - rp[1] * dw[0]));
-    constexpr long long kLim = 1ll << 48;
-    return t[0] > -kLim && t[0] < kLim && t[1] > -kLim && t[1] < kLim && t[2] > -kLim && t[2] < kLim;
+    const double l[3] = {mj * (rp[1] * dw[2] - rp[2] * dw[1]), mj * (rp[2] * dw[0] - rp[0] * dw[2]),
+                         mj * (rp[0] * dw[1] - rp[1] * dw[0])};
+    bool ok = true;
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+        // rounded to an integer by adding 1.5 2^52, whose low bits then hold
+        // it (below 2^51 in magnitude; larger terms are refused)
+        constexpr double kMagic = 6755399441055744.0;
+        const double y = l[e] * 4294967296.0 + kMagic;
+        t[e] = __double_as_longlong(y) - 0x4338000000000000ll;
+        ok = ok && fabs(y - kMagic) < 281474976710656.0;   // 2^48
+    }
+    return ok;
 }
 
 // omega = -I^+ dL with I = tr(Q) 1 - Q (pseudo-inverse: rank-deficient cells,

@@ -355,9 +355,46 @@ __device__ __forceinline__ double exact_term(float v)
 // sums, reservation and stores, of which 5 per CU overlap.
 // The instance for equal masses without particle ids is held to 5 waves per
 // SIMD (96 registers), those with ids or 8 slots per thread to 4.
-template <int kT, int kS, bool kMass, bool kWide, bool kIds>
+// Angular-momentum rule: one particle's terms of the first pass into its
+// cell's record.  Equal masses: the twelve sums are held in FP64 (rounded to
+// integers below 2^40, so additions are exact in any order, as in exact_term,
+// and no 64-bit conversion is needed); per-particle masses in 64-bit integers.
+__device__ __forceinline__ void am_add(unsigned long long* ra, bool has_mass, float m, float vx, float vy, float vz,
+                                       const double rl[3])
+{
+    if (has_mass) {
+        long long tm[kAmMoments];
+        am_moments((double)m, vx, vy, vz, rl, tm);
+#pragma unroll
+        for (int q = 0; q < kAmMoments; ++q) atomicAdd(&ra[q], (unsigned long long)tm[q]);
+    } else {
+        double tm[kAmMoments];
+        am_moments_exact(vx, vy, vz, rl, tm);
+        double* const rd = reinterpret_cast<double*>(ra);
+#pragma unroll
+        for (int q = 1; q < kAmMoments; ++q) unsafeAtomicAdd(&rd[q], tm[q]);
+    }
+    atomicAdd(&ra[kAmMoments], 1ull);   // particle count (free until pass 2a)
+}
+
+// ... and of the second pass (record: u, r_c, n); false when a term is out of range.
+__device__ __forceinline__ bool am_add_dl(unsigned long long* ra, float m, float vx, float vy, float vz,
+                                          const double rl[3], double ca, double sa)
+{
+    const double* const rec = reinterpret_cast<const double*>(ra);
+    long long tl3[3];
+    const bool ok = am_dl((double)m, vx, vy, vz, rl, rec, rec + 3, rec + 6, ca, sa, tl3);
+#pragma unroll
+    for (int e = 0; e < 3; ++e) atomicAdd(&ra[15 + e], (unsigned long long)tl3[e]);
+    return ok;
+}
+
+// Waves per SIMD of the angular-momentum instances.
+constexpr int am_waves(int slots) { return slots > 6 ? 3 : 4; }
+
+template <int kT, int kS, bool kMass, bool kAM, bool kWide, bool kIds>
 __global__ __launch_bounds__(kT)
-__attribute__((amdgpu_waves_per_eu(kMass ? 1 : (kIds || kS > 6 ? 4 : 5), kMass || kIds || kS > 6 ? 8 : 5)))
+__attribute__((amdgpu_waves_per_eu(kAM ? am_waves(kS) : kMass ? 1 : (kIds || kS > 6 ? 4 : 5), kMass || kIds || kS > 6 ? 8 : 5)))
 void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __restrict__ boxes,
                   const BoxState* __restrict__ st, long long* __restrict__ dacc)
 {
@@ -365,7 +402,8 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
     // records (equal masses: three FP64 sums and a 32-bit count; per-particle
     // masses: four 64-bit integers and a count), then the collision map in
     // 48-byte records (three 16-byte reads); both strides spread neighbouring
-    // cells over the LDS banks.
+    // cells over the LDS banks.  Boxes with the angular-momentum rule (kAM
+    // instances only) use kAmWords per cell instead.
     extern __shared__ __align__(16) unsigned long long lds64[];
     constexpr int kWaves = kT / kWave;
     // destination groups: 27 neighbour bricks (13 = this one), then the
@@ -393,9 +431,10 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
     const int ey = min(1 << b.bshift[1], b.L[1] - loy);
     const int ez = min(1 << b.bshift[2], b.L[2] - loz);
     const int ncl = ex * ey * ez;
+    const bool am = kAM && b.conserve_l != 0;
     unsigned long long* const acc = lds64;   // [ncl][kAccWords]
     float* const fu = reinterpret_cast<float*>(lds64 + ((kAccWords * ncl + 1) & ~1));   // [ncl][kUnWords]
-    for (int i = threadIdx.x; i < kAccWords * ncl; i += kT) lds64[i] = 0ull;
+    for (int i = threadIdx.x; i < (am ? kAmWords : kAccWords) * ncl; i += kT) lds64[i] = 0ull;
     const uint32_t beg = (uint32_t)uniform((int)gp(b.bstart)[brick]);
     // escape sums for this brick (overflow particles of the previous step):
     // flagged during that step, in the half of eflag this step only reads,
@@ -496,6 +535,12 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
         for (int u = 0; u < kS; ++u) {
             const uint32_t c = meta[u];
             if (c == kNone) continue;
+            if (kAM && am) {
+                double rl[3];
+                am_local(b.a, px[u], py[u], pz[u], sh, rl);
+                am_add(acc + c * kAmWords, has_mass, kMass ? pm[u] : 1.0f, vx[u], vy[u], vz[u], rl);
+                continue;
+            }
             unsigned long long* const r = acc + c * kAccWords;
             if (kMass) {
                 const float mi = pm[u];
@@ -517,6 +562,33 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
     __syncthreads();
     const bool flagged = eflag_k == stamp;
     const uint32_t L0 = (uint32_t)b.L[0], L01 = (uint32_t)b.L[0] * (uint32_t)b.L[1];
+    // Angular-momentum rule, flagged brick: the particles of this step's
+    // overflow bucket whose collision cell lies here are read directly (pass
+    // 1: moments, pass 2: angular-momentum change), as their escape sums
+    // carry no moments.
+    auto am_overflow = [&](int pass) {
+        const uint32_t nbk = (uint32_t)b.nbrick;
+        const uint32_t ob = gp(b.bstart)[nbk];
+        const uint32_t ocnt = min(gp(b.bsize[src])[nbk], gp(b.bstart)[nbk + 1] - ob);
+        for (uint32_t q = threadIdx.x; q < ocnt; q += kT) {
+            const uint32_t si = ob + q;
+            const float ux = gp(b.p[src][3])[si], uy = gp(b.p[src][4])[si], uz = gp(b.p[src][5])[si];
+            const float qx = fold(fmaf(ux, dt, gp(b.p[src][0])[si]), b.len[0]);
+            const float qy = fold(fmaf(uy, dt, gp(b.p[src][1])[si]), b.len[1]);
+            const float qz = fold(fmaf(uz, dt, gp(b.p[src][2])[si]), b.len[2]);
+            const int cx = axis_cell(qx, sh.x, inv_a, b.L[0]) - lox;
+            const int cy = axis_cell(qy, sh.y, inv_a, b.L[1]) - loy;
+            const int cz = axis_cell(qz, sh.z, inv_a, b.L[2]) - loz;
+            if ((unsigned)cx >= (unsigned)ex || (unsigned)cy >= (unsigned)ey || (unsigned)cz >= (unsigned)ez) continue;
+            const int c = cx + ex * (cy + ey * cz);
+            const float mj = has_mass ? gp(b.m[src])[si] : 1.0f;
+            double rl[3];
+            am_local(b.a, qx, qy, qz, sh, rl);
+            unsigned long long* const ra = acc + c * kAmWords;
+            if (pass == 1) am_add(ra, has_mass, mj, ux, uy, uz, rl);
+            else if (!am_add_dl(ra, mj, ux, uy, uz, rl, b.ca, b.sa)) viol += 1;
+        }
+    };
     if (flagged) {   // overflow particles of this step whose cells lie here
         MPCD_G CellAcc* __restrict__ esc = gp(b.esc[k & 1]);
         for (int c = threadIdx.x; c < ncl; c += kT) {
@@ -525,7 +597,9 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
             const CellAcc e = load_acc(esc + gc);
             if (e.w) {
                 unsigned long long* const r = acc + c * kAccWords;
-                if (kMass) {
+                if (kAM && am) {
+                    // the particles themselves are read below
+                } else if (kMass) {
                     r[0] += e.sx;
                     r[1] += e.sy;
                     r[2] += e.sz;
@@ -546,10 +620,70 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
                 store_acc(esc + gc, z);
             }
         }
+        if (kAM && am) am_overflow(1);
         __syncthreads();
     }
 
     // 2. cell velocity and axis
+    if (kAM && am) {
+        // 2a. per cell: u, r_c, axis n, second moment Q (FP64, in place of
+        // the moment sums; an empty cell keeps n = 0)
+        for (int c = threadIdx.x; c < ncl; c += kT) {
+            unsigned long long* const ra = acc + c * kAmWords;
+            if (ra[kAmMoments] == 0) continue;
+            if (ra[kAmMoments] >= kMaxCellCount) viol += 1;   // the cell's sums may have wrapped
+            const int lx = c % ex, ly = (c / ex) % ey, lz = c / (ex * ey);
+            const uint32_t gc = (uint32_t)(lox + lx) + L0 * (uint32_t)(loy + ly) + L01 * (uint32_t)(loz + lz);
+            double* const rec = reinterpret_cast<double*>(ra);
+            double S[kAmMoments], uc[3], rc[3], Q[6], n[3];
+            S[0] = has_mass ? fixed_to_double(ra[0]) : fixed_to_double(ra[kAmMoments] << 32);
+#pragma unroll
+            for (int e = 1; e < kAmMoments; ++e) S[e] = has_mass ? fixed_to_double(ra[e]) : rec[e];
+            am_cell(b, k, gc, S, uc, rc, Q, n);
+            for (int e = 0; e < 3; ++e) {
+                rec[e] = uc[e];
+                rec[3 + e] = rc[e];
+                rec[6 + e] = n[e];
+            }
+            for (int e = 0; e < 6; ++e) rec[9 + e] = Q[e];
+        }
+        __syncthreads();
+        // 2b. angular-momentum change of each particle under the plain rotation
+        for (int ch = nch - 1; ch >= 0; --ch) {
+            if (nch > 1) load(ch);
+#pragma unroll
+            for (int u = 0; u < kS; ++u) {
+                const uint32_t c = meta[u];
+                if (c == kNone) continue;
+                double rl[3];
+                am_local(b.a, px[u], py[u], pz[u], sh, rl);
+                if (!am_add_dl(acc + c * kAmWords, kMass ? pm[u] : 1.0f, vx[u], vy[u], vz[u], rl, b.ca, b.sa)) viol += 1;
+            }
+        }
+        if (flagged) am_overflow(2);
+        __syncthreads();
+        // 2c. per cell: omega (in place of Q); flagged bricks publish the
+        // cell data for the overflow particles
+        for (int c = threadIdx.x; c < ncl; c += kT) {
+            unsigned long long* const ra = acc + c * kAmWords;
+            double* const rec = reinterpret_cast<double*>(ra);
+            if (rec[6] == 0.0 && rec[7] == 0.0 && rec[8] == 0.0) continue;   // empty
+            double om[3];
+            am_omega(rec + 9, reinterpret_cast<const long long*>(ra + 15), om);
+            for (int e = 0; e < 3; ++e) rec[9 + e] = om[e];
+            if (flagged) {
+                const int lx = c % ex, ly = (c / ex) % ey, lz = c / (ex * ey);
+                const uint32_t gc = (uint32_t)(lox + lx) + L0 * (uint32_t)(loy + ly) + L01 * (uint32_t)(loz + lz);
+                CellAm* const g = b.uam + gc;
+                for (int e = 0; e < 3; ++e) {
+                    g->u[e] = rec[e];
+                    g->rc[e] = rec[3 + e];
+                    g->n[e] = rec[6 + e];
+                    g->om[e] = om[e];
+                }
+            }
+        }
+    } else
     for (int c = threadIdx.x; c < ncl; c += kT) {
         const unsigned long long* const r = acc + c * kAccWords;
         const unsigned long long w = kMass ? r[3] : ((r[3] & 0xffffffffull) << 32);
@@ -623,7 +757,15 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
             const uint32_t i = index_of(ch, u);
             bool stay = false;
             if (i < cnt) {
-                if (c != kNone) {
+                if (kAM && am && c != kNone) {
+                    const double* const rec = reinterpret_cast<const double*>(acc + c * kAmWords);
+                    double rl[3];
+                    am_local(b.a, px[u], py[u], pz[u], sh, rl);
+                    const float3 v = am_velocity(vx[u], vy[u], vz[u], rl, rec, rec + 3, rec + 6, rec + 9, b.ca, b.sa);
+                    vx[u] = v.x;
+                    vy[u] = v.y;
+                    vz[u] = v.z;
+                } else if (c != kNone) {
                     const float4* const q = reinterpret_cast<const float4*>(fu + c * kUnWords);
                     const float4 q0 = q[0], q1 = q[1], q2 = q[2];
                     CellRot cr;
@@ -764,461 +906,6 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
         if (ch + 1 < nch) __syncthreads();
     }
     step_flush_wave(viol, vsum, vacf, dacc + (size_t)uniform(tl.box) * kAccLanes * 3, blockIdx.x);
-}
-
-// The same step for launches that hold a box with the angular-momentum rule
-// (boxes without it, with and without masses and ids, are served as well).
-template <int kT, int kS>
-__global__ __launch_bounds__(kT)
-void k_brick_step_am(const Tile* __restrict__ tiles, int one_box, const BoxDev* __restrict__ boxes,
-                  const BoxState* __restrict__ st, long long* __restrict__ dacc)
-{
-    // LDS, per cell of the brick: exact sums of m v (3 x 64 bit) and of m (64
-    // bit, or a 32-bit count for equal masses) in 40-byte records, then u_c,
-    // n_c and kappa in 48-byte records (two 16-byte reads); both strides
-    // spread neighbouring cells over the LDS banks.  Boxes with the
-    // angular-momentum rule (kAM instances only) use kAmWords per cell instead.
-    constexpr bool kMass = true, kAM = true, kWide = true, kIds = true;
-    extern __shared__ __align__(16) unsigned long long lds64[];
-    __shared__ uint32_t gcnt[27], gpos[27], gbeg[27], gcap[27];
-    constexpr uint32_t kChunk = (uint32_t)kT * kS;
-    constexpr uint32_t kNone = 0xffffffffu;   // no particle / no cell
-    const int t = xcd_tile(blockIdx.x, gridDim.x);
-    // with a single brick box the brick tiles are its bricks in order, and
-    // the tile record need not be loaded before the box's
-    const Tile tl = one_box >= 0 ? Tile{one_box, 0, t, t + 1} : tiles[t];
-    const BoxState s = st[uniform(tl.box)];
-    const BoxDev& b = boxes[uniform(tl.box)];
-    if (box_idle(s) || b.binning != 1) return;
-    const int brick = uniform((int)tl.begin);
-    const long long k = uniform(s.k);
-    const int src = uniform(s.parity), dst = src ^ 1;
-    const bool vacf = b.vacf_stride > 0 && ((k + 1 - uniform(s.vacf_origin)) % b.vacf_stride) == 0;
-    const int nb0 = b.nb[0], nb1 = b.nb[1], nb2 = b.nb[2];
-    const int bx = brick % nb0, by = (brick / nb0) % nb1, bz = brick / (nb0 * nb1);
-    const int lox = brick_lo(bx, b.bshift[0]), loy = brick_lo(by, b.bshift[1]), loz = brick_lo(bz, b.bshift[2]);
-    const int ex = min(1 << b.bshift[0], b.L[0] - lox);
-    const int ey = min(1 << b.bshift[1], b.L[1] - loy);
-    const int ez = min(1 << b.bshift[2], b.L[2] - loz);
-    const int ncl = ex * ey * ez;
-    const bool am = kAM && b.conserve_l != 0;
-    unsigned long long* const acc = lds64;   // [ncl][kAccWords]: sx, sy, sz, w
-    float* const fu = reinterpret_cast<float*>(lds64 + ((kAccWords * ncl + 1) & ~1));   // [ncl][kUnWords]
-    for (int i = threadIdx.x; i < (am ? kAmWords : kAccWords) * ncl; i += kT) lds64[i] = 0ull;
-    const uint32_t beg = (uint32_t)uniform((int)gp(b.bstart)[brick]);
-    // escape sums for this brick (overflow particles of the previous step):
-    // flagged during that step, in the half of eflag this step only reads,
-    // so the load goes out with the bucket's and is not waited for here
-    const uint32_t stamp = (uint32_t)(k + 1);
-    const uint32_t eflag_k = gp(b.eflag)[(size_t)(k & 1) * b.nbrick + brick];
-    // the bucket's fill, read by every wave (this workgroup alone reads it and
-    // clears it at the end, since this buffer is the next step's destination)
-    const uint32_t cnt = min((uint32_t)uniform((int)gp(b.bsize[src])[brick]),
-                             (uint32_t)uniform((int)gp(b.bstart)[brick + 1]) - beg);
-    __syncthreads();
-    const int nch = (int)((cnt + kChunk - 1) / kChunk);
-
-    // bucket-relative bases (uniform): a lane's offset is its index in the bucket
-    const MPCD_G float* __restrict__ ix = ugp(b.p[src][0]) + beg;
-    const MPCD_G float* __restrict__ iy = ugp(b.p[src][1]) + beg;
-    const MPCD_G float* __restrict__ iz = ugp(b.p[src][2]) + beg;
-    const MPCD_G float* __restrict__ ivx = ugp(b.p[src][3]) + beg;
-    const MPCD_G float* __restrict__ ivy = ugp(b.p[src][4]) + beg;
-    const MPCD_G float* __restrict__ ivz = ugp(b.p[src][5]) + beg;
-    const bool has_mass = kMass && b.m[src] != nullptr;   // uniform
-    const MPCD_G float* __restrict__ im = has_mass ? ugp(b.m[src]) + beg : nullptr;
-    const float3 sh = grid_shift(b, k);
-    const float dt = b.dt;
-    const float inv_a = b.inv_a;
-
-    float px[kS], py[kS], pz[kS], vx[kS], vy[kS], vz[kS], pm[kS];
-    uint32_t meta[kS];   // cell in the brick after loading; destination group << 24 | rank later
-    long long d[kNumDiag] = {};
-    // load and stream chunk ch; meta <- cell inside the brick, kNone past the
-    // end of the bucket or for a particle in the wrong bucket (never happens:
-    // both sides use the same arithmetic; flagged if it does)
-    // slots of chunk ch that hold particles for some thread (uniform)
-    auto used_slots = [&](int ch) -> int {
-        const uint32_t rem = cnt - (uint32_t)ch * kChunk;
-        return (int)min((uint32_t)kS, (rem + kT - 1) / kT);
-    };
-    auto load = [&](int ch) {
-        const int nu = used_slots(ch);
-#pragma unroll
-        for (int u = 0; u < kS; ++u) {   // issue every load first
-            if (u >= nu) break;
-            const uint32_t i = (uint32_t)ch * kChunk + (uint32_t)(u * kT) + threadIdx.x;
-            const uint32_t o = (i < cnt ? i : 0u) * 4u;   // byte offset inside the bucket
-            px[u] = ldg(ix, o);
-            py[u] = ldg(iy, o);
-            pz[u] = ldg(iz, o);
-            vx[u] = ldg(ivx, o);
-            vy[u] = ldg(ivy, o);
-            vz[u] = ldg(ivz, o);
-            pm[u] = has_mass ? ldg(im, o) : 1.0f;
-        }
-#pragma unroll
-        for (int u = 0; u < kS; ++u) {
-            if (u >= nu) {
-                meta[u] = kNone;
-                continue;
-            }
-            const uint32_t i = (uint32_t)ch * kChunk + (uint32_t)(u * kT) + threadIdx.x;
-            px[u] = fold(fmaf(vx[u], dt, px[u]), b.len[0]);
-            py[u] = fold(fmaf(vy[u], dt, py[u]), b.len[1]);
-            pz[u] = fold(fmaf(vz[u], dt, pz[u]), b.len[2]);
-            const int cx = axis_cell_raw(px[u], sh.x, inv_a, b.L[0]) - lox;   // range-checked below
-            const int cy = axis_cell_raw(py[u], sh.y, inv_a, b.L[1]) - loy;
-            const int cz = axis_cell_raw(pz[u], sh.z, inv_a, b.L[2]) - loz;
-            const bool in = (unsigned)cx < (unsigned)ex && (unsigned)cy < (unsigned)ey && (unsigned)cz < (unsigned)ez;
-            meta[u] = (i < cnt && in) ? (uint32_t)(cx + ex * (cy + ey * cz)) : kNone;
-            if (i < cnt && !in) d[5] += 1;
-        }
-    };
-
-    // 1. cell sums; the last chunk first, so that chunk 0 stays in registers
-    for (int ch = nch - 1; ch >= 0; --ch) {
-        load(ch);
-#pragma unroll
-        for (int u = 0; u < kS; ++u) {
-            const uint32_t c = meta[u];
-            if (c == kNone) continue;
-            if (kAM && am) {   // moments of the angular-momentum rule
-                double rl[3];
-                long long tm[kAmMoments];
-                am_local(b.a, px[u], py[u], pz[u], sh, rl);
-                am_moments((double)pm[u], vx[u], vy[u], vz[u], rl, tm);
-                unsigned long long* const ra = acc + (size_t)c * kAmWords;
-#pragma unroll
-                for (int q = 0; q < kAmMoments; ++q) atomicAdd(&ra[q], (unsigned long long)tm[q]);
-                atomicAdd(&ra[kAmMoments], 1ull);   // particle count (free until pass 2a)
-                continue;
-            }
-            unsigned long long* const r = acc + (size_t)c * kAccWords;
-            if (kMass) {
-                const float mi = pm[u];
-                atomicAdd(&r[0], to_fixed(mi * vx[u]));
-                atomicAdd(&r[1], to_fixed(mi * vy[u]));
-                atomicAdd(&r[2], to_fixed(mi * vz[u]));
-                atomicAdd(&r[3], to_fixed(mi));
-                atomicAdd(reinterpret_cast<uint32_t*>(&r[4]), 1u);   // particle count
-            } else {   // equal masses: r[3] counts particles
-                atomicAdd(&r[0], to_fixed(vx[u]));
-                atomicAdd(&r[1], to_fixed(vy[u]));
-                atomicAdd(&r[2], to_fixed(vz[u]));
-                atomicAdd(reinterpret_cast<uint32_t*>(&r[3]), 1u);
-            }
-        }
-    }
-    __syncthreads();
-    const bool flagged = eflag_k == stamp;
-    const uint32_t L0 = (uint32_t)b.L[0], L01 = (uint32_t)b.L[0] * (uint32_t)b.L[1];
-    // Angular-momentum rule, flagged brick: the particles of this step's
-    // overflow bucket whose collision cell lies here are read directly (pass
-    // 1: moments, pass 2: angular-momentum change), as their escape sums
-    // carry no moments.
-    auto am_overflow = [&](int pass) {
-        const uint32_t nbk = (uint32_t)b.nbrick;
-        const uint32_t ob = gp(b.bstart)[nbk];
-        const uint32_t ocnt = min(gp(b.bsize[src])[nbk], gp(b.bstart)[nbk + 1] - ob);
-        for (uint32_t q = threadIdx.x; q < ocnt; q += kT) {
-            const uint32_t si = ob + q;
-            const float ux = gp(b.p[src][3])[si], uy = gp(b.p[src][4])[si], uz = gp(b.p[src][5])[si];
-            const float qx = fold(fmaf(ux, dt, gp(b.p[src][0])[si]), b.len[0]);
-            const float qy = fold(fmaf(uy, dt, gp(b.p[src][1])[si]), b.len[1]);
-            const float qz = fold(fmaf(uz, dt, gp(b.p[src][2])[si]), b.len[2]);
-            const int cx = axis_cell(qx, sh.x, inv_a, b.L[0]) - lox;
-            const int cy = axis_cell(qy, sh.y, inv_a, b.L[1]) - loy;
-            const int cz = axis_cell(qz, sh.z, inv_a, b.L[2]) - loz;
-            if ((unsigned)cx >= (unsigned)ex || (unsigned)cy >= (unsigned)ey || (unsigned)cz >= (unsigned)ez) continue;
-            const int c = cx + ex * (cy + ey * cz);
-            const double mj = has_mass ? (double)gp(b.m[src])[si] : 1.0;
-            double rl[3];
-            am_local(b.a, qx, qy, qz, sh, rl);
-            unsigned long long* const ra = acc + (size_t)c * kAmWords;
-            if (pass == 1) {
-                long long tm[kAmMoments];
-                am_moments(mj, ux, uy, uz, rl, tm);
-                for (int e = 0; e < kAmMoments; ++e) atomicAdd(&ra[e], (unsigned long long)tm[e]);
-                atomicAdd(&ra[kAmMoments], 1ull);
-            } else {
-                const double* const rec = reinterpret_cast<const double*>(ra);
-                long long tl3[3];
-                if (!am_dl(mj, ux, uy, uz, rl, rec, rec + 3, rec + 6, b.ca, b.sa, tl3)) d[5] += 1;
-                for (int e = 0; e < 3; ++e) atomicAdd(&ra[15 + e], (unsigned long long)tl3[e]);
-            }
-        }
-    };
-    if (flagged) {   // overflow particles of this step whose cells lie here
-        MPCD_G CellAcc* __restrict__ esc = gp(b.esc[k & 1]);
-        for (int c = threadIdx.x; c < ncl; c += kT) {
-            const int lx = c % ex, ly = (c / ex) % ey, lz = c / (ex * ey);
-            const uint32_t gc = (uint32_t)(lox + lx) + L0 * (uint32_t)(loy + ly) + L01 * (uint32_t)(loz + lz);
-            const CellAcc e = load_acc(esc + gc);
-            if (e.w) {
-                if (!(kAM && am)) {
-                    unsigned long long* const r = acc + (size_t)c * kAccWords;
-                    r[0] += e.sx;
-                    r[1] += e.sy;
-                    r[2] += e.sz;
-                    r[3] += kMass ? e.w : (e.w >> 32);   // escape weights are 2^32 m
-                    if (kMass && has_mass) {   // and their count
-                        MPCD_G uint32_t* const ec = gp(b.ecnt[k & 1]) + gc;
-                        *reinterpret_cast<uint32_t*>(&r[4]) += *ec;
-                        *ec = 0u;
-                    }
-                }
-                CellAcc z = {0ull, 0ull, 0ull, 0ull};
-                store_acc(esc + gc, z);
-            }
-        }
-        if (kAM && am) am_overflow(1);
-        __syncthreads();
-    }
-
-    if (kAM && am) {
-        // 2a. per cell: u, r_c, axis n, second moment Q (FP64, in place of
-        // the moment sums; an empty cell keeps n = 0)
-        for (int c = threadIdx.x; c < ncl; c += kT) {
-            unsigned long long* const ra = acc + (size_t)c * kAmWords;
-            const long long* const sm = reinterpret_cast<const long long*>(ra);
-            if (sm[0] == 0) continue;
-            if (ra[kAmMoments] >= kMaxCellCount) d[5] += 1;   // the cell's sums may have wrapped
-            const int lx = c % ex, ly = (c / ex) % ey, lz = c / (ex * ey);
-            const uint32_t gc = (uint32_t)(lox + lx) + L0 * (uint32_t)(loy + ly) + L01 * (uint32_t)(loz + lz);
-            double uc[3], rc[3], Q[6], n[3];
-            am_cell(b, k, gc, sm, uc, rc, Q, n);
-            double* const rec = reinterpret_cast<double*>(ra);
-            for (int e = 0; e < 3; ++e) {
-                rec[e] = uc[e];
-                rec[3 + e] = rc[e];
-                rec[6 + e] = n[e];
-            }
-            for (int e = 0; e < 6; ++e) rec[9 + e] = Q[e];
-        }
-        __syncthreads();
-        // 2b. angular-momentum change of each particle under the plain rotation
-        for (int ch = nch - 1; ch >= 0; --ch) {
-            if (nch > 1) load(ch);
-#pragma unroll
-            for (int u = 0; u < kS; ++u) {
-                const uint32_t c = meta[u];
-                if (c == kNone) continue;
-                unsigned long long* const ra = acc + (size_t)c * kAmWords;
-                const double* const rec = reinterpret_cast<const double*>(ra);
-                double rl[3];
-                long long tl3[3];
-                am_local(b.a, px[u], py[u], pz[u], sh, rl);
-                if (!am_dl((double)pm[u], vx[u], vy[u], vz[u], rl, rec, rec + 3, rec + 6, b.ca, b.sa, tl3)) d[5] += 1;
-                for (int e = 0; e < 3; ++e) atomicAdd(&ra[15 + e], (unsigned long long)tl3[e]);
-            }
-        }
-        if (flagged) am_overflow(2);
-        __syncthreads();
-        // 2c. per cell: omega (in place of Q); flagged bricks publish the
-        // cell data for the overflow particles
-        for (int c = threadIdx.x; c < ncl; c += kT) {
-            unsigned long long* const ra = acc + (size_t)c * kAmWords;
-            double* const rec = reinterpret_cast<double*>(ra);
-            if (rec[6] == 0.0 && rec[7] == 0.0 && rec[8] == 0.0) continue;   // empty
-            double om[3];
-            am_omega(rec + 9, reinterpret_cast<const long long*>(ra + 15), om);
-            for (int e = 0; e < 3; ++e) rec[9 + e] = om[e];
-            if (flagged) {
-                const int lx = c % ex, ly = (c / ex) % ey, lz = c / (ex * ey);
-                const uint32_t gc = (uint32_t)(lox + lx) + L0 * (uint32_t)(loy + ly) + L01 * (uint32_t)(loz + lz);
-                CellAm* const g = b.uam + gc;
-                for (int e = 0; e < 3; ++e) {
-                    g->u[e] = rec[e];
-                    g->rc[e] = rec[3 + e];
-                    g->n[e] = rec[6 + e];
-                    g->om[e] = om[e];
-                }
-            }
-        }
-        __syncthreads();
-    } else {
-        // 2. cell velocity and axis
-        for (int c = threadIdx.x; c < ncl; c += kT) {
-            const unsigned long long* const r = acc + (size_t)c * kAccWords;
-            const unsigned long long w = kMass ? r[3] : ((r[3] & 0xffffffffull) << 32);
-            if (w == 0) continue;
-            const uint32_t count = kMass ? (uint32_t)r[4] : (uint32_t)r[3];
-            if (count >= kMaxCellCount) d[5] += 1;   // the cell's sums may have wrapped
-            const int lx = c % ex, ly = (c / ex) % ey, lz = c / (ex * ey);
-            const uint32_t gc = (uint32_t)(lox + lx) + L0 * (uint32_t)(loy + ly) + L01 * (uint32_t)(loz + lz);
-            double uc[3];
-            fixed_mean3(r[0], r[1], r[2], w, uc);
-            const CellRot cr = cell_rotation(uc[0], uc[1], uc[2], cell_axis(b, k, gc), b.ca, b.sa);
-            float4* const q = reinterpret_cast<float4*>(fu + (size_t)c * kUnWords);
-            q[0] = make_float4(cr.m[0], cr.m[1], cr.m[2], cr.m[3]);
-            q[1] = make_float4(cr.m[4], cr.m[5], cr.m[6], cr.m[7]);
-            q[2] = make_float4(cr.m[8], cr.t[0], cr.t[1], cr.t[2]);
-            if (flagged) store_rot(gp(b.un) + gc, cr);   // read by the overflow particles
-        }
-        __syncthreads();
-    }
-
-    // 3./4. rotate, route to the next step's buckets, store
-    const float3 sh1 = grid_shift(b, k + 1);
-    // Interior bricks (a full brick below and above this one, itself full,
-    // along every axis): a particle that stays inside the box needs no
-    // periodic fold, and the brick of its next cell c = floor((x' - s1)/a),
-    // c in [-1, L], is c >> shift, a neighbour exactly when that is within
-    // one of this brick's index (c = -1 and c = L, the images of cells L-1
-    // and 0, then fall outside the three); everything else takes the exact
-    // general form.
-    const bool interior = bx >= 1 && ((bx + 2) << b.bshift[0]) <= b.L[0] && by >= 1 &&
-                          ((by + 2) << b.bshift[1]) <= b.L[1] && bz >= 1 && ((bz + 2) << b.bshift[2]) <= b.L[2];
-    MPCD_G float* const ox = ugp(b.p[dst][0]);
-    MPCD_G float* const oy = ugp(b.p[dst][1]);
-    MPCD_G float* const oz = ugp(b.p[dst][2]);
-    MPCD_G float* const ovx = ugp(b.p[dst][3]);
-    MPCD_G float* const ovy = ugp(b.p[dst][4]);
-    MPCD_G float* const ovz = ugp(b.p[dst][5]);
-    const bool has_id = kIds && b.pid[src] != nullptr;   // uniform
-    MPCD_G int32_t* const oid = has_id ? ugp(b.pid[dst]) : nullptr;
-    const MPCD_G int32_t* const iid = has_id ? ugp(b.pid[src]) + beg : nullptr;   // bucket-relative
-    const bool has_m = kMass && b.m[src] != nullptr;
-    const int lane = threadIdx.x & (kWave - 1);
-    const unsigned long long below = (1ull << lane) - 1ull;
-    for (int ch = 0; ch < nch; ++ch) {
-        if (ch > 0) load(ch);
-        const int nu = used_slots(ch);
-        if (threadIdx.x < 27) gcnt[threadIdx.x] = 0u;
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < kS; ++u) {
-            if (u >= nu) {
-                meta[u] = 28u << 24;
-                continue;
-            }
-            const uint32_t i = (uint32_t)ch * kChunk + (uint32_t)(u * kT) + threadIdx.x;
-            uint32_t r = 28u;   // no particle
-            if (i < cnt) {
-                const uint32_t c = meta[u];
-                if (kAM && am && c != kNone) {
-                    const double* const rec = reinterpret_cast<const double*>(acc + (size_t)c * kAmWords);
-                    double rl[3];
-                    am_local(b.a, px[u], py[u], pz[u], sh, rl);
-                    const float3 v = am_velocity(vx[u], vy[u], vz[u], rl, rec, rec + 3, rec + 6, rec + 9, b.ca, b.sa);
-                    vx[u] = v.x;
-                    vy[u] = v.y;
-                    vz[u] = v.z;
-                } else if (c != kNone) {
-                    const float4* const q = reinterpret_cast<const float4*>(fu + (size_t)c * kUnWords);
-                    const float4 q0 = q[0], q1 = q[1], q2 = q[2];
-                    CellRot cr;
-                    cr.m[0] = q0.x; cr.m[1] = q0.y; cr.m[2] = q0.z; cr.m[3] = q0.w;
-                    cr.m[4] = q1.x; cr.m[5] = q1.y; cr.m[6] = q1.z; cr.m[7] = q1.w;
-                    cr.m[8] = q2.x; cr.t[0] = q2.y; cr.t[1] = q2.z; cr.t[2] = q2.w;
-                    const float3 v = apply_rotation(cr, vx[u], vy[u], vz[u]);
-                    vx[u] = v.x;
-                    vy[u] = v.y;
-                    vz[u] = v.z;
-                }
-                const float3 v = make_float3(vx[u], vy[u], vz[u]);
-                diag_check(d, v);
-                if (vacf) vacf_term(b, ldg(iid, i * 4u), v, d);
-                // brick of the next collision cell (a non-finite position
-                // lands far away and takes the clamped slow path below)
-                const float qx = fmaf(v.x, dt, px[u]), qy = fmaf(v.y, dt, py[u]), qz = fmaf(v.z, dt, pz[u]);
-                int rx, ry, rz;
-                if (interior && qx >= 0.0f && qx < b.len[0] && qy >= 0.0f && qy < b.len[1] && qz >= 0.0f &&
-                    qz < b.len[2]) {
-                    rx = ((int)floorf((qx - sh1.x) * inv_a) >> b.bshift[0]) - bx;
-                    ry = ((int)floorf((qy - sh1.y) * inv_a) >> b.bshift[1]) - by;
-                    rz = ((int)floorf((qz - sh1.z) * inv_a) >> b.bshift[2]) - bz;
-                } else {
-                    const int dbx = brick_of(axis_cell_raw(fold(qx, b.len[0]), sh1.x, inv_a, b.L[0]), b.bshift[0]);
-                    const int dby = brick_of(axis_cell_raw(fold(qy, b.len[1]), sh1.y, inv_a, b.L[1]), b.bshift[1]);
-                    const int dbz = brick_of(axis_cell_raw(fold(qz, b.len[2]), sh1.z, inv_a, b.L[2]), b.bshift[2]);
-                    rx = brick_rel(bx, dbx, nb0);
-                    ry = brick_rel(by, dby, nb1);
-                    rz = brick_rel(bz, dbz, nb2);
-                }
-                r = ((unsigned)(rx + 1) <= 2u && (unsigned)(ry + 1) <= 2u && (unsigned)(rz + 1) <= 2u)
-                        ? (uint32_t)((rx + 1) + 3 * ((ry + 1) + 3 * (rz + 1)))
-                        : 27u;
-            }
-            // particles that stay in the brick (most) take consecutive ranks
-            // per wave, so their stores coalesce
-            const unsigned long long mask = __ballot(r == 13u);
-            uint32_t rank = 0u;
-            if (mask) {
-                const int leader = __ffsll((long long)mask) - 1;
-                uint32_t wb = 0u;
-                if (lane == leader) wb = atomicAdd(&gcnt[13], (uint32_t)__popcll(mask));
-                wb = __builtin_amdgcn_readlane(wb, leader);
-                rank = wb + (uint32_t)__popcll(mask & below);
-            }
-            if (r < 27u && r != 13u) rank = atomicAdd(&gcnt[r], 1u);
-            meta[u] = (r << 24) | rank;
-        }
-        // identities (only needed for the store): load while the groups reserve
-        int32_t id[kS];
-#pragma unroll
-        for (int u = 0; u < kS; ++u) {
-            if (u >= nu || !has_id) break;
-            const uint32_t i = (uint32_t)ch * kChunk + (uint32_t)(u * kT) + threadIdx.x;
-            id[u] = ldg(iid, (i < cnt ? i : 0u) * 4u);
-        }
-        __syncthreads();
-        if (threadIdx.x < 27) {
-            const int q = threadIdx.x;
-            const uint32_t n = gcnt[q];
-            if (n) {
-                const int dx = brick_nbr(bx, q % 3 - 1, nb0), dy = brick_nbr(by, (q / 3) % 3 - 1, nb1),
-                          dz = brick_nbr(bz, q / 9 - 1, nb2);
-                const uint32_t dest = (uint32_t)(dx + nb0 * (dy + nb1 * dz));
-                gpos[q] = gatomic_add(gp(b.bsize[dst]) + dest, n);
-                const uint32_t b0 = gp(b.bstart)[dest];
-                gbeg[q] = b0;
-                gcap[q] = gp(b.bstart)[dest + 1] - b0;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < kS; ++u) {
-            if (u >= nu) break;
-            const uint32_t r = meta[u] >> 24;
-            if (r >= 28u) continue;
-            const float3 v = make_float3(vx[u], vy[u], vz[u]);
-            uint32_t j = 0u;
-            bool placed = false;
-            if (r < 27u) {
-                const uint32_t p = gpos[r] + (meta[u] & 0xffffffu);
-                if (p < gcap[r]) {
-                    j = gbeg[r] + p;
-                    placed = true;
-                }
-            }
-            if (!placed) {   // far (or full) destination: slow path
-                const int3 nc = next_cell(b, px[u], py[u], pz[u], v, sh1);
-                const int3 db = brick_of_cell(b, nc);
-                if (r == 27u) placed = place_single(b, dst, (uint32_t)(db.x + nb0 * (db.y + nb1 * db.z)), &j);
-                if (!placed) placed = place_overflow(b, dst, k, nc, pm[u], v, &j);
-            }
-            if (!placed) {
-                d[5] += 1;
-                continue;
-            }
-            // byte offset of destination slot j (64-bit for buffers of 2^30 slots or more)
-            typedef typename std::conditional<kWide, unsigned long long, uint32_t>::type Off;
-            const Off o = (Off)j * 4u;
-            stg(ox, o, px[u]);
-            stg(oy, o, py[u]);
-            stg(oz, o, pz[u]);
-            stg(ovx, o, v.x);
-            stg(ovy, o, v.y);
-            stg(ovz, o, v.z);
-            if (has_id) stg(oid, o, id[u]);
-            if (has_m) stg(gp(b.m[dst]), o, pm[u]);
-        }
-        if (ch + 1 < nch) __syncthreads();
-    }
-    step_flush<kT>(d, vacf, dacc + (size_t)uniform(tl.box) * kAccLanes * 3, blockIdx.x);
-    if (threadIdx.x == 0) gp(b.bsize[src])[brick] = 0u;   // after every wave read it (step_flush's barrier)
 }
 
 // Particles of the overflow bucket of the current buffer (one workgroup per
@@ -1696,8 +1383,10 @@ __device__ __forceinline__ void collide_cell_am(const BoxDev& b, int par, long l
 #pragma unroll
         for (int q = 0; q < kAmMoments; ++q) sm[q] += t[q];
     }
-    double u[3], rc[3], Q[6], n[3], om[3];
-    am_cell(b, k, c, sm, u, rc, Q, n);
+    double S[kAmMoments], u[3], rc[3], Q[6], n[3], om[3];
+#pragma unroll
+    for (int q = 0; q < kAmMoments; ++q) S[q] = fixed_to_double((unsigned long long)sm[q]);
+    am_cell(b, k, c, S, u, rc, Q, n);
     long long sl[3] = {0, 0, 0};
     for (uint32_t j = beg; j < end; ++j) {
         double r[3];
@@ -2531,39 +2220,34 @@ static void brick_step_launch(K kern, int threads, bool& attr, const Tables& T, 
     hipLaunchKernelGGL(kern, dim3(T.nbtiles), dim3(threads), T.brick_lds + 16, s, T.btiles, T.brick_box, T.boxes,
                        T.state, T.dacc);
 }
-template <int kT, int kS, bool kMass, bool kWide, bool kIds>
+template <int kT, int kS, bool kMass, bool kAM, bool kWide, bool kIds>
 static void brick_step_run(const Tables& T, hipStream_t s)
 {
     static bool attr = false;
-    brick_step_launch(k_brick_step<kT, kS, kMass, kWide, kIds>, kT, attr, T, s);
-}
-template <int kT, int kS>
-static void brick_step_run_am(const Tables& T, hipStream_t s)
-{
-    static bool attr = false;
-    brick_step_launch(k_brick_step_am<kT, kS>, kT, attr, T, s);
+    brick_step_launch(k_brick_step<kT, kS, kMass, kAM, kWide, kIds>, kT, attr, T, s);
 }
 // Instances: plain without particle ids, plain and per-particle masses with
 // 32-bit store offsets (every brick buffer below 2^30 slots), masses with
-// 64-bit offsets, and the angular-momentum rule (64-bit offsets; compute
-// bound).  The masses instances also serve boxes without masses, and every
+// 64-bit offsets, and the angular-momentum rule with and without masses
+// (64-bit offsets; compute bound).  The masses instances also serve boxes without masses, and every
 // instance but the first serves boxes with and without ids.
 template <int kT, int kS>
 static void brick_step_at(const Tables& T, hipStream_t s)
 {
-    if (T.brick_am) brick_step_run_am<kT, kS>(T, s);
-    else if (T.brick_wide) brick_step_run<kT, kS, true, true, true>(T, s);
-    else if (T.brick_mass) brick_step_run<kT, kS, true, false, true>(T, s);
-    else if (T.brick_ids) brick_step_run<kT, kS, false, false, true>(T, s);
-    else brick_step_run<kT, kS, false, false, false>(T, s);
+    if (T.brick_am && T.brick_mass) brick_step_run<kT, kS, true, true, true, true>(T, s);
+    else if (T.brick_am) brick_step_run<kT, kS, false, true, true, true>(T, s);
+    else if (T.brick_wide) brick_step_run<kT, kS, true, false, true, true>(T, s);
+    else if (T.brick_mass) brick_step_run<kT, kS, true, false, false, true>(T, s);
+    else if (T.brick_ids) brick_step_run<kT, kS, false, false, false, true>(T, s);
+    else brick_step_run<kT, kS, false, false, false, false>(T, s);
 }
 
 // Small grids: one instance for boxes with and without ids, one for masses.
 template <int kT, int kS>
 static void brick_step_small(const Tables& T, hipStream_t s)
 {
-    if (T.brick_mass) brick_step_run<kT, kS, true, false, true>(T, s);
-    else brick_step_run<kT, kS, false, false, true>(T, s);
+    if (T.brick_mass) brick_step_run<kT, kS, true, false, false, true>(T, s);
+    else brick_step_run<kT, kS, false, false, false, true>(T, s);
 }
 
 // Launch shapes of the brick step (workgroup size, particles per thread),
