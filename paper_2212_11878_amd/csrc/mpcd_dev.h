@@ -594,14 +594,44 @@ __device__ __forceinline__ void rotate_w(double nx, double ny, double nz, double
     out[2] = pz + ca * (w[2] - pz) + sa * (nx * w[1] - ny * w[0]);
 }
 
+// Every further Jacobi rotation of `a` (rotations so far in v) would leave the
+// diagonal and v as they are, bit for bit.  With rho >= t, the largest angle to
+// come (4 off / gap: the off-diagonal sum over the smallest difference of two
+// diagonal entries, with room for the sweeps left), c = 1 exactly, no term
+// added to a diagonal entry exceeds rho (off + low + rho amax) and none added
+// to an entry of v exceeds 2 rho: all below half a unit in the last place.
+// (`low`, the sum below the diagonal, holds the roundings of earlier sweeps;
+// the angles come from above it.  Convergence is quadratic: the loop's own
+// end, 1e-300, comes two or three sweeps later, and the rotations were the
+// longest phase of the rule: 14 of 53 us of a workgroup, now 7.)
+__host__ __device__ __forceinline__ bool jacobi_settled(const double a[3][3], const double v[3][3], double off)
+{
+#pragma clang fp contract(off)
+    const double e0 = fabs(a[0][0]), e1 = fabs(a[1][1]), e2 = fabs(a[2][2]);
+    const double amax = fmax(e0, fmax(e1, e2)), dmin = fmin(e0, fmin(e1, e2));
+    if (!(off < 1e-15 * amax)) return false;
+    const double gap = fmin(fabs(a[0][0] - a[1][1]), fmin(fabs(a[0][0] - a[2][2]), fabs(a[1][1] - a[2][2])));
+    if (!(gap > 1e-12 * amax)) return false;
+    double vmin = fabs(v[0][0]);
+#pragma unroll
+    for (int i = 1; i < 9; ++i) vmin = fmin(vmin, fabs(v[i / 3][i % 3]));
+    const double low = fabs(a[1][0]) + fabs(a[2][0]) + fabs(a[2][1]);
+    if (!(low < 1e-14 * amax)) return false;
+    const double rho = 4.0 * off / gap;
+    return 5.0 * rho * (off + low + rho * amax) < 1e-17 * dmin && 2.0 * rho < 1e-17 * vmin;
+}
+
 // Moore-Penrose pseudo-inverse of a symmetric 3x3 matrix a[3][3] by cyclic
 // Jacobi rotations (eigenvalues below tol times the largest count as zero).
-__device__ __forceinline__ void sym3_pinv(double a[3][3], double tol, double out[3][3])
+template <bool kEarly = true>
+__host__ __device__ __forceinline__ void sym3_pinv(double a[3][3], double tol, double out[3][3])
 {
 #pragma clang fp contract(off)
     double v[3][3] = {{1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
     for (int sweep = 0; sweep < 12; ++sweep) {
-        if (fabs(a[0][1]) + fabs(a[0][2]) + fabs(a[1][2]) < 1e-300) break;
+        const double off = fabs(a[0][1]) + fabs(a[0][2]) + fabs(a[1][2]);
+        if (off < 1e-300) break;
+        if (kEarly && jacobi_settled(a, v, off)) break;
 #pragma unroll
         for (int pq = 0; pq < 3; ++pq) {
             const int p = pq == 2 ? 1 : 0, q = pq == 0 ? 1 : 2;

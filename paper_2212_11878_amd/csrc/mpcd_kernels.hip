@@ -624,11 +624,14 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
         __syncthreads();
     }
 
-    // 2. cell velocity and axis
+    // 2. cell velocity and axis.  A brick has fewer cells than the workgroup
+    // threads; which of its waves take them differs between the workgroups of
+    // a CU, or the same two SIMDs would do the cell work of all of them.
+    const int tcell = (int)(threadIdx.x ^ (((blockIdx.x >> 8) & (kWaves - 1)) * kWave));
     if (kAM && am) {
         // 2a. per cell: u, r_c, axis n, second moment Q (FP64, in place of
         // the moment sums; an empty cell keeps n = 0)
-        for (int c = threadIdx.x; c < ncl; c += kT) {
+        for (int c = tcell; c < ncl; c += kT) {
             unsigned long long* const ra = acc + c * kAmWords;
             if (ra[kAmMoments] == 0) continue;
             if (ra[kAmMoments] >= kMaxCellCount) viol += 1;   // the cell's sums may have wrapped
@@ -664,7 +667,7 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
         __syncthreads();
         // 2c. per cell: omega (in place of Q); flagged bricks publish the
         // cell data for the overflow particles
-        for (int c = threadIdx.x; c < ncl; c += kT) {
+        for (int c = tcell; c < ncl; c += kT) {
             unsigned long long* const ra = acc + c * kAmWords;
             double* const rec = reinterpret_cast<double*>(ra);
             if (rec[6] == 0.0 && rec[7] == 0.0 && rec[8] == 0.0) continue;   // empty
@@ -684,7 +687,7 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
             }
         }
     } else
-    for (int c = threadIdx.x; c < ncl; c += kT) {
+    for (int c = tcell; c < ncl; c += kT) {
         const unsigned long long* const r = acc + c * kAccWords;
         const unsigned long long w = kMass ? r[3] : ((r[3] & 0xffffffffull) << 32);
         if (w == 0) continue;
