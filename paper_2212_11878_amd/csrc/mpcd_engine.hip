@@ -1156,7 +1156,7 @@ int mpcd_get_state(mpcd_ctx* c, int32_t slot, float* xyzv, int64_t* step)
     if (n > 0 && sl->dev.pid[0]) {   // particle-id order, put together on the device
         float* stage_dev = nullptr;
         const float* const stage = state_stage(c, n, &stage_dev);
-        launch_state_by_id(c->T, slot, sl->ntile, n, sl->part, c->report_dev, stage_dev, c->stream);
+        launch_state_by_id(c->T, slot, sl->dev.nslot, n, sl->part, c->report_dev, stage_dev, c->stream);
         HIPCHK(hipGetLastError());
         HIPCHK(hipStreamSynchronize(c->stream));
         c->short_calls = 0;

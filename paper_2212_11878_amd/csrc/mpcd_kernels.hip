@@ -913,14 +913,14 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
 
 // Particles of the overflow bucket of the current buffer (one workgroup per
 // box, after the brick step): the same step, with the cell data the flagged
-// bricks published.  Adds their diagnostics to d.
-__device__ void overflow_step(const BoxDev& b, const BoxState& s, long long (&d)[kNumDiag])
+// bricks published.  Adds their diagnostics to d; returns their number.
+__device__ uint32_t overflow_step(const BoxDev& b, const BoxState& s, long long (&d)[kNumDiag])
 {
     const int src = s.parity, dst = s.parity ^ 1;
     const uint32_t nbk = (uint32_t)b.nbrick;
     const uint32_t ob = gp(b.bstart)[nbk];
     const uint32_t cnt = min(gp(b.bsize[src])[nbk], gp(b.bstart)[nbk + 1] - ob);
-    if (cnt == 0) return;
+    if (cnt == 0) return 0u;
     const float3 sh = grid_shift(b, s.k), sh1 = grid_shift(b, s.k + 1);
     const bool has_m = b.m[src] != nullptr;
     const bool vacf = vacf_due(b, s);
@@ -955,6 +955,7 @@ __device__ void overflow_step(const BoxDev& b, const BoxState& s, long long (&d)
         if (vacf) vacf_term(b, id, v, d);
         put_particle(b, dst, j, x, y, z, v, id, m, has_m);
     }
+    return cnt;
 }
 
 // Re-bucketing step, first kernel: mark the holes of the current buffer
@@ -1691,45 +1692,51 @@ __global__ __launch_bounds__(kBlock) void k_box_finish(const int32_t* __restrict
 {
     const int bx = active[blockIdx.x];
     BoxState* sp = &st[bx];
+    // one workgroup per box, bound by its chain of loads: what does not depend
+    // on the overflow bucket is read before it, and a step that takes no sample
+    // reduces nothing (0.3 us less of an 11 us step of a 10^3 box)
+    long long* const l = dacc + ((size_t)bx * kAccLanes + (threadIdx.x & (kAccLanes - 1))) * 3;
+    const long long marks = threadIdx.x < kAccLanes ? l[2] : 0;
     if (box_idle(*sp)) return;
     const BoxDev& b = boxes[bx];
     const bool by_cell = (b.binning == 2);
+    uint32_t left = 0u;   // particles the step put into the overflow bucket
+    if (!by_cell && threadIdx.x == 0) left = gp(b.bsize[sp->parity ^ 1])[b.nbrick];
     long long d[kNumDiag] = {};
-    if (!by_cell) overflow_step(b, *sp, d);
-    // this thread's share of the exact sums: its particles plus, for the
-    // first kAccLanes threads, one accumulator lane (then cleared)
-    long long hi = d[4] >> 32, lo = (long long)(unsigned long long)(unsigned)(d[4] & 0xffffffffll), viol = d[5];
-    long long* a = dacc + (size_t)bx * kAccLanes * 3;
-    if (threadIdx.x < kAccLanes) {
-        long long* l = a + (size_t)threadIdx.x * 3;
-        hi += l[0];
-        lo += l[1];
-        viol += l[2];
-        l[0] = 0;
-        l[1] = 0;
-        l[2] = 0;
-    }
-    __shared__ long long red[3][kBlock / kWave];
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    hi = wave_sum(hi);
-    lo = wave_sum(lo);
-    viol = wave_sum(viol);
-    if (lane == 0) {
-        red[0][w] = hi;
-        red[1][w] = lo;
-        red[2][w] = viol;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        long long th = 0, tl = 0, tv = 0;
-        for (int i = 0; i < kBlock / kWave; ++i) {
-            th += red[0][i];
-            tl += red[1][i];
-            tv += red[2][i];
+    const uint32_t drained = by_cell ? 0u : overflow_step(b, *sp, d);
+    // the range check: this thread's particles and accumulator lane; on
+    // sampled steps the VACF sum likewise, reduced over the workgroup
+    const bool vac = vacf_due(b, *sp);
+    if (marks) l[2] = 0;
+    const long long viol = d[5] + marks;
+    const bool out_of_range = __syncthreads_or(viol != 0) != 0;
+    __shared__ long long red[2][kBlock / kWave];
+    if (vac) {
+        long long hi = d[4] >> 32, lo = (long long)(unsigned long long)(unsigned)(d[4] & 0xffffffffll);
+        if (threadIdx.x < kAccLanes) {
+            hi += l[0];
+            lo += l[1];
+            l[0] = 0;
+            l[1] = 0;
         }
+        const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+        hi = wave_sum(hi);
+        lo = wave_sum(lo);
+        if (lane == 0) {
+            red[0][w] = hi;
+            red[1][w] = lo;
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        long long th = 0, tl = 0;
+        if (vac)
+            for (int i = 0; i < kBlock / kWave; ++i) {
+                th += red[0][i];
+                tl += red[1][i];
+            }
         const double vsum = (double)th + (double)tl * 2.3283064365386963e-10;   // (hi 2^32 + lo) 2^-32
-        const bool vac = vacf_due(b, *sp);
-        if (tv != 0) sp->status = -5;   // velocity out of range / not finite
+        if (out_of_range) sp->status = -5;   // velocity out of range / not finite
         if (vac && sp->vacf_len < b.vacf_cap && b.n > 0)
             b.vacf[sp->vacf_len++] = vsum / (double)b.n;
         if (!by_cell) {
@@ -1737,7 +1744,8 @@ __global__ __launch_bounds__(kBlock) void k_box_finish(const int32_t* __restrict
             gp(b.bsize[src])[nbk] = 0u;   // overflow bucket drained
             // particles left in the overflow bucket: ask the host for a
             // re-bucketing (new capacities) at its next step call
-            if (gp(b.bsize[src ^ 1])[nbk] != 0u) {
+            if (drained) left = gp(b.bsize[src ^ 1])[nbk];
+            if (left != 0u) {
                 sp->overflow_steps += 1;
                 sp->rebucket = 1;
                 if (host_flag) __hip_atomic_store(host_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -1883,21 +1891,32 @@ __global__ __launch_bounds__(kBlock) void k_snapshot(const BoxDev* __restrict__ 
 // touches; the host used to fetch every slot and id (2.24 x 7 words a
 // particle) and scatter them itself: 32^3 cells 3.1 -> 0.53 ms a dump, 100^3
 // cells 205 -> 24 ms.
+// (In tiles of kStateTile slots: of small boxes that leaves a wave a few of
+// their small buckets, where a kPartTile took 23 us for an 8^3 box, now 6.)
+constexpr int kStateTile = kPartTile / 4;   // at most 4 counts per kPartTile: they share its kNumDiag partials
 __global__ __launch_bounds__(kBlock) void k_state_by_id(const BoxDev* __restrict__ boxes,
                                                          const BoxState* __restrict__ st, int box,
                                                          long long* __restrict__ counts)
 {
-    const Tile tl = box_tile(boxes, box);
     const BoxDev& b = boxes[box];
+    const int64_t begin = (int64_t)blockIdx.x * kStateTile;
+    const Tile tl{box, 0, begin, min(b.nslot, begin + (int64_t)kStateTile)};
     const int par = uniform(st[box].parity);
     const int64_t n = b.n;
     MPCD_G float* const out = ugp(b.p[par ^ 1][0]);   // the six fields of a buffer follow each other
+    const MPCD_G int32_t* const pid = ugp(b.pid[par]);
+    const MPCD_G float* in[6];
+#pragma unroll
+    for (int d = 0; d < 6; ++d) in[d] = ugp(b.p[par][d]);
     long long good = 0;
     for_live(b, par, tl, [&](int64_t i) {
-        const int64_t id = gp(b.pid[par])[i];
+        const int64_t id = pid[i];
+        float v[6];
+#pragma unroll
+        for (int d = 0; d < 6; ++d) v[d] = in[d][i];
         if (id < 0 || id >= n) return;
 #pragma unroll
-        for (int d = 0; d < 6; ++d) out[d * n + id] = gp(b.p[par][d])[i];
+        for (int d = 0; d < 6; ++d) out[d * n + id] = v[d];
         ++good;
     });
     __shared__ long long red[kBlock / kWave];
@@ -2365,12 +2384,13 @@ void launch_mark_holes_box(const Tables& T, int32_t box, int ntile, hipStream_t 
     MPCD_LAUNCH(k_mark_holes, ntile, kBlock, s, nullptr, T.boxes, T.state, 1, box);
 }
 static int stride_grid(int64_t n) { return (int)std::min<int64_t>((n + kBlock - 1) / kBlock, 2048); }
-void launch_state_by_id(const Tables& T, int32_t box, int ntile, int64_t n, long long* counts, BoxReport* report,
-                        float* host, hipStream_t s)
+void launch_state_by_id(const Tables& T, int32_t box, int64_t nslot, int64_t n, long long* counts,
+                        BoxReport* report, float* host, hipStream_t s)
 {
-    MPCD_LAUNCH(k_state_by_id, ntile, kBlock, s, T.boxes, T.state, box, counts);
+    const int nt = (int)((nslot + kStateTile - 1) / kStateTile);
+    MPCD_LAUNCH(k_state_by_id, nt, kBlock, s, T.boxes, T.state, box, counts);
     MPCD_LAUNCH(k_state_report, host ? std::max(1, stride_grid(6 * n)) : 1, kBlock, s, T.boxes, T.state, box, counts,
-                ntile, report, host);
+                nt, report, host);
 }
 void launch_state_load(const Tables& T, int32_t box, int to, int64_t n, const float* host, BoxReport* report,
                        hipStream_t s)

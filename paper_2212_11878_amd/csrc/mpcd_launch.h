@@ -60,8 +60,8 @@ void launch_box_stats(const Tables& T, int32_t box, int ntile, long long* part, 
                       double mass, BoxReport* report, hipStream_t s);   // consumes the partials
 // a box's state in id order into its idle buffer, box state and count of valid
 // particles into `report`, and the state into `host` (pinned) if given
-void launch_state_by_id(const Tables& T, int32_t box, int ntile, int64_t n, long long* counts, BoxReport* report,
-                        float* host, hipStream_t s);
+void launch_state_by_id(const Tables& T, int32_t box, int64_t nslot, int64_t n, long long* counts,
+                        BoxReport* report, float* host, hipStream_t s);
 // a new state of n particles in buffer `to` (from `host`, pinned, if given),
 // checked: report->count becomes 1 on a bad value
 void launch_state_load(const Tables& T, int32_t box, int to, int64_t n, const float* host, BoxReport* report,
