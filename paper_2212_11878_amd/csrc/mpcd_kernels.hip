@@ -1768,7 +1768,7 @@ __global__ __launch_bounds__(kBlock) void k_init_maxwell(const BoxDev* __restric
     const Tile tl = box_tile(boxes, box);
     const BoxDev& b = boxes[tl.box];
     const int par = st[tl.box].parity;
-    long long d[kNumDiag] = {};
+    DiagSums sums;
     for (int64_t i = tl.begin + threadIdx.x; i < tl.end; i += kBlock) {
         if (i >= b.n) {   // spare slot of a brick box
             mark_hole(b, par, i);
@@ -1790,9 +1790,10 @@ __global__ __launch_bounds__(kBlock) void k_init_maxwell(const BoxDev* __restric
         b.p[par][4][i] = vy;
         b.p[par][5][i] = vz;
         if (b.pid[par]) b.pid[par][i] = (int32_t)i;
-        diag_particle(d, make_float3(vx, vy, vz), 1.0f);
+        diag_add(sums, make_float3(vx, vy, vz), 1.0f);
     }
-    block_diag(d, partials + (size_t)t * kNumDiag);
+    diag_close(sums);
+    block_diag(sums.d, partials + (size_t)t * kNumDiag);
 }
 
 // v <- (v - V) * scale with (V, scale) = the box state's adj[]; partial
@@ -1807,7 +1808,7 @@ __global__ __launch_bounds__(kBlock) void k_init_adjust(const BoxDev* __restrict
     const int par = st[tl.box].parity;
     const float mx = st[tl.box].adj[0], my = st[tl.box].adj[1], mz = st[tl.box].adj[2];
     const float scale = st[tl.box].adj[3];
-    long long d[kNumDiag] = {};
+    DiagSums sums;
     for (int64_t i = tl.begin + threadIdx.x; i < tl.end; i += kBlock) {
         if (!slot_live(b, par, i)) continue;
         const float vx = (b.p[par][3][i] - mx) * scale;
@@ -1816,9 +1817,10 @@ __global__ __launch_bounds__(kBlock) void k_init_adjust(const BoxDev* __restrict
         b.p[par][3][i] = vx;
         b.p[par][4][i] = vy;
         b.p[par][5][i] = vz;
-        diag_particle(d, make_float3(vx, vy, vz), 1.0f);
+        diag_add(sums, make_float3(vx, vy, vz), 1.0f);
     }
-    block_diag(d, partials + (size_t)t * kNumDiag);
+    diag_close(sums);
+    block_diag(sums.d, partials + (size_t)t * kNumDiag);
 }
 
 // f(i) for every slot i of the tile that holds a particle of buffer `par`.
@@ -1857,8 +1859,8 @@ __device__ __forceinline__ void for_live(const BoxDev& b, int par, const Tile& t
     }
 }
 
-// v0 <- v, and the exact partials of the current state (sum m v, sum m v^2,
-// sum v.v0)
+// The exact partials of the current state (sum m v, sum m v^2); with set_v0
+// also v0 <- v and sum v.v0
 __global__ __launch_bounds__(kBlock) void k_snapshot(const BoxDev* __restrict__ boxes,
                                                       const BoxState* __restrict__ st, int box,
                                                       int set_v0, long long* __restrict__ partials)
@@ -1867,22 +1869,22 @@ __global__ __launch_bounds__(kBlock) void k_snapshot(const BoxDev* __restrict__ 
     const Tile tl = box_tile(boxes, box);
     const BoxDev& b = boxes[tl.box];
     const int par = uniform(st[tl.box].parity);
-    const bool has_v0 = b.vacf_stride > 0;
+    const bool new_v0 = b.vacf_stride > 0 && set_v0;
     const MPCD_G float* const px = ugp(b.p[par][3]);
     const MPCD_G float* const py = ugp(b.p[par][4]);
     const MPCD_G float* const pz = ugp(b.p[par][5]);
     const MPCD_G float* const pm = b.m[par] ? ugp(b.m[par]) : nullptr;
-    long long d[kNumDiag] = {};
+    DiagSums sums;
     for_live(b, par, tl, [&](int64_t i) {
         const float3 v = make_float3(px[i], py[i], pz[i]);
-        if (has_v0) {
-            const int32_t id = gp(b.pid[par])[i];
-            if (set_v0) b.v0[id] = make_float4(v.x, v.y, v.z, 0.0f);
-            vacf_term(b, id, v, d);
+        if (new_v0) {   // and sample 0 of the series
+            b.v0[gp(b.pid[par])[i]] = make_float4(v.x, v.y, v.z, 0.0f);
+            diag_vacf(sums.d, v, v.x, v.y, v.z);
         }
-        diag_particle(d, v, pm ? pm[i] : 1.0f);
+        diag_add(sums, v, pm ? pm[i] : 1.0f);
     });
-    block_diag(d, partials + (size_t)t * kNumDiag);
+    diag_close(sums);
+    block_diag(sums.d, partials + (size_t)t * kNumDiag);
 }
 
 // The state of one box, in the order of its particle ids, into the idle
@@ -2178,11 +2180,27 @@ __global__ __launch_bounds__(kBlock) void k_moments_tiles(const float* __restric
                                                            const float* __restrict__ vz, const float* __restrict__ m,
                                                            int64_t n, long long* __restrict__ partials)
 {
+    // Bound by the reads (12 or 16 B a particle), once a term costs a few
+    // instructions: eight particles per thread are in flight.
+    constexpr int kU = 8;
     const int64_t begin = (int64_t)blockIdx.x * kPartTile, end = min(n, begin + (int64_t)kPartTile);
-    long long d[kNumDiag] = {};
-    for (int64_t i = begin + threadIdx.x; i < end; i += kBlock)
-        diag_particle(d, make_float3(vx[i], vy[i], vz[i]), m ? m[i] : 1.0f);
-    block_diag(d, partials + (size_t)blockIdx.x * kNumDiag);
+    DiagSums sums;
+    for (int64_t i0 = begin + threadIdx.x; i0 < end; i0 += (int64_t)kBlock * kU) {
+        float x[kU], y[kU], z[kU], w[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int64_t i = i0 + (int64_t)u * kBlock, j = i < end ? i : begin;
+            x[u] = vx[j];
+            y[u] = vy[j];
+            z[u] = vz[j];
+            w[u] = m ? m[j] : 1.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u)
+            if (i0 + (int64_t)u * kBlock < end) diag_add(sums, make_float3(x[u], y[u], z[u]), w[u]);
+    }
+    diag_close(sums);
+    block_diag(sums.d, partials + (size_t)blockIdx.x * kNumDiag);
 }
 
 __global__ __launch_bounds__(kStatBlock) void k_moments_finish(const long long* __restrict__ partials, int ntile,

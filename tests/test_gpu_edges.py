@@ -48,6 +48,26 @@ def test_moments_over_record_counts(mp, tiles, extra):
     assert abs(got[3] - want[3]) <= n * 2.0 ** -32 + 4.0 * 2.0 ** -53 * v2
 
 
+@pytest.mark.parametrize("n", [1, 255, 4096, 9000])
+def test_moments_at_the_edges_of_their_fast_range(mp, n):
+    """Energies on both sides of 2^18 and velocities and masses on both sides
+    of their limits, in multiples of 2^-8 or 2^-4: every product is exact, so
+    the sums are those of integers, and each particle out of range counts once."""
+    import torch
+    rng = np.random.default_rng(n)
+    edge = np.array([[32.0, 0, 0], [31.9375, 0, 0], [0, -32.0625, 0], [0, 255.9375, -255.9375], [256.0, 1, 1],
+                     [0, 0, -256.0], [-255.9375, 255.9375, 255.9375], [0.0625, -0.0625, 0], [0, 0, 0], [300.0, 2, 3]])
+    vel = edge[rng.integers(0, len(edge), n)].T.astype(np.float32)
+    mass = np.array([256.0, 256.0625, 2.0 ** -8, 2.0 ** -9, 1.0, 255.9375])[rng.integers(0, 6, n)].astype(np.float32)
+    v, m = torch.from_numpy(np.ascontiguousarray(vel)).cuda(), torch.from_numpy(mass).cuda()
+    out = torch.zeros(5, dtype=torch.float64, device="cuda")
+    rc = mp.mpcd_moments_noalloc(v[0].data_ptr(), v[1].data_ptr(), v[2].data_ptr(), m.data_ptr(), n, out.data_ptr())
+    torch.cuda.synchronize()
+    assert rc == mp.MPCD_OK
+    out_of_range = (np.abs(vel) >= 256.0).any(axis=0) | (mass < 2.0 ** -8) | (mass > 256.0)
+    assert list(out.cpu().numpy()) == exact_moments(vel, mass) + [float(out_of_range.sum())]
+
+
 @pytest.mark.parametrize("L,density", [((60, 60, 61), 8.6), ((100, 90, 91), 8.1)])
 def test_observe_over_record_counts(mp, L, density):
     """Boxes on both sides of the reduction's second level: the observables
