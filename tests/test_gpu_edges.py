@@ -206,3 +206,24 @@ def test_small_bricks_only_while_they_fit(mp):
         a, b, c = ctx.get_state(slots[0]), ctx.get_state(slots[1]), tight.get_state(slots_tight[0])
     for x in (b, c):
         assert np.array_equal(a[0], x[0]) and np.array_equal(a[1], x[1])
+
+
+@pytest.mark.parametrize("scale", [1.0, 32.0, 200.0])
+@pytest.mark.parametrize("density", [1, 9, 300])
+def test_sort_sums_beyond_their_fast_range(mp, scale, density):
+    """Momenta below, around and above 2^10 (the range that counting-sort
+    binning sums in FP64): the bits of bricks, which sum integers throughout."""
+    L, n = (9, 8, 7), density * 504
+    rng = np.random.default_rng(density)
+    pos = inputs.thermal_state(L, n, seed=n)[0]
+    vel = rng.uniform(-scale, scale, (3, n)).astype(np.float32)
+    mass = rng.uniform(min(scale, 30.0), scale + 1.0, n).astype(np.float32)
+    out = []
+    for binning in (mp.MPCD_BIN_ATOMIC, mp.MPCD_BIN_SORT):
+        with mp.Context(binning=binning, brick=2) as ctx:
+            slot = ctx.admit(mp.make_desc(L, n, init="external", seed=3, dt=0.003, particle_mass=True))
+            ctx.set_state(slot, (pos, vel))
+            ctx.set_mass(slot, mass)
+            ctx.step(3)
+            out.append(ctx.get_state(slot))
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
