@@ -27,7 +27,9 @@
 //
 // Per box, outside the step: k_init_maxwell / k_init_adjust (initial state),
 // k_snapshot (exact momentum and energy on demand), k_box_stats(_tiles)
-// (exact 128-bit reduction of their per-tile partials on the device).
+// (exact 128-bit reduction of their per-tile partials on the device),
+// k_state_by_id / k_state_load / k_state_report (a state to and from the order
+// of the particle ids, with the reports that the host waits for).
 //
 // Both paths sum the momentum of a cell exactly (64-bit fixed point), so
 // they produce bit-identical velocities whatever the order of the atomics.
@@ -2305,8 +2307,9 @@ static void brick_step_run(const Tables& T, hipStream_t s)
 // Instances: plain without particle ids, plain and per-particle masses with
 // 32-bit store offsets (every brick buffer below 2^30 slots), masses with
 // 64-bit offsets, and the angular-momentum rule with and without masses
-// (64-bit offsets; compute bound).  The masses instances also serve boxes without masses, and every
-// instance but the first serves boxes with and without ids.
+// (64-bit offsets; compute bound).  The masses instances also serve boxes
+// without masses, and every instance but the first serves boxes with and
+// without ids.
 template <int kT, int kS>
 static void brick_step_at(const Tables& T, hipStream_t s)
 {
