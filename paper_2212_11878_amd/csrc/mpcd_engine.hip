@@ -263,7 +263,7 @@ Layout box_layout(int64_t n, int64_t nslot, int64_t ncell, bool vacf, int vacf_c
     Layout L{};
     size_t o = 0;
     const size_t pf = align256((size_t)nslot * 4);
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < 2; ++b)   // the six arrays of a buffer in one stretch
         for (int d = 0; d < 6; ++d) { L.off_p[b][d] = o; o += pf; }
     L.off_v0 = o;
     if (vacf) o += align256((size_t)n * 16);
@@ -509,7 +509,7 @@ int enqueue_step(mpcd_ctx* c, bool with_sort)
         STEP_K(K_ZERO, launch_zero_counts(T, s));
         STEP_K(K_COUNT, launch_count(T, s));
         STEP_K(K_SCAN, launch_scan(T, s));
-        STEP_K(K_SCATTER, launch_scatter(T, s));
+        STEP_K(K_SCATTER, launch_scatter(T, s); if (with_sort && c->any_brick) launch_unpack(T, s));
         STEP_K(K_FLIP, launch_flip(T, s));
     }
     if (c->any_brick) STEP_K(K_BRICK_STEP, launch_brick_step(T, s));

@@ -16,7 +16,8 @@
 //                         reduce diagnostics, VACF sample, k++
 //   Re-bucketing (after admission / set_state, or when a bucket overflowed):
 //     k_mark_holes, k_rebucket_clear, then the counting sort below keyed by
-//     brick, which also sets the bucket capacities
+//     brick, which also sets the bucket capacities and scatters records, and
+//     k_unpack, which lays them out as arrays in the buffer they came from
 //
 //   SORT binning (counting sort by collision cell every step)
 //     zero, k_count (streamed collision cell + rank), scan, k_scatter (the
@@ -1201,8 +1202,8 @@ __global__ __launch_bounds__(kBlock) void k_scan_box(const int32_t* __restrict__
 }
 
 // per cell tile: exclusive scan of the key capacities into starts.  For
-// brick boxes the keys are bricks, and the starts become the bucket layout of
-// the buffer the scatter fills (counts plus slack; overflow bucket last).
+// brick boxes the keys are bricks, and the starts become the bucket layout
+// (counts plus slack; overflow bucket last) of the buffer that k_unpack fills.
 __global__ __launch_bounds__(kBlock) void k_scan_apply(const Tile* __restrict__ tiles,
                                                         const BoxDev* __restrict__ boxes,
                                                         const BoxState* __restrict__ st,
@@ -1235,13 +1236,13 @@ __global__ __launch_bounds__(kBlock) void k_scan_apply(const Tile* __restrict__ 
             b.cstart[c] = run;
             if (brick && c < nbk) {
                 b.bstart[c] = run;
-                b.bsize[s.parity ^ 1][c] = cnt[j];
-                b.bsize[s.parity][c] = 0u;   // the next step's destination
+                b.bsize[s.parity][c] = cnt[j];
+                b.bsize[s.parity ^ 1][c] = 0u;   // the next step's destination
                 if (c == nbk - 1) {         // overflow bucket: the rest of the buffer
                     b.bstart[nbk] = run + cap[j];
                     b.bstart[nbk + 1] = (uint32_t)b.nslot;
-                    b.bsize[s.parity ^ 1][nbk] = 0u;
                     b.bsize[s.parity][nbk] = 0u;
+                    b.bsize[s.parity ^ 1][nbk] = 0u;
                 }
             }
         }
@@ -1249,6 +1250,10 @@ __global__ __launch_bounds__(kBlock) void k_scan_apply(const Tile* __restrict__ 
     }
     if (tl.end == b.ncell && threadIdx.x == 0) b.cstart[b.ncell] = brick ? tilesum[t] + total : (uint32_t)b.n;
 }
+
+// six floats of a record at a multiple of 24 bytes
+typedef float Rec4 __attribute__((ext_vector_type(4), aligned(8)));
+typedef float Rec2 __attribute__((ext_vector_type(2), aligned(8)));
 
 __global__ __launch_bounds__(kBlock) void k_scatter(const Tile* __restrict__ tiles,
                                                      const BoxDev* __restrict__ boxes,
@@ -1259,7 +1264,7 @@ __global__ __launch_bounds__(kBlock) void k_scatter(const Tile* __restrict__ til
     const BoxDev& b = boxes[uniform(tl.box)];
     if (box_idle(s) || !sort_due(b, s)) return;
     const int src = uniform(s.parity), dst = src ^ 1;
-    const bool stream = (b.binning == 2);
+    const bool stream = (b.binning == 2);   // otherwise records (k_unpack)
     const bool has_m = b.m[src] != nullptr;
     const float dt = b.dt;
     const MPCD_G float* __restrict__ ix = ugp(b.p[src][0]);
@@ -1332,20 +1337,72 @@ __global__ __launch_bounds__(kBlock) void k_scatter(const Tile* __restrict__ til
             if (!live[u]) continue;
             const int64_t i = i0 + (int64_t)u * kBlock;
             const int64_t j = (int64_t)cstart[key[u]] + rk[u];
-            float px = qx[u], py = qy[u], pz = qz[u];
             if (stream) {
-                px = fold(fmaf(ux[u], dt, px), b.len[0]);
-                py = fold(fmaf(uy[u], dt, py), b.len[1]);
-                pz = fold(fmaf(uz[u], dt, pz), b.len[2]);
+                ox[j] = fold(fmaf(ux[u], dt, qx[u]), b.len[0]);
+                oy[j] = fold(fmaf(uy[u], dt, qy[u]), b.len[1]);
+                oz[j] = fold(fmaf(uz[u], dt, qz[u]), b.len[2]);
+                ovx[j] = ux[u];
+                ovy[j] = uy[u];
+                ovz[j] = uz[u];
+            } else {
+                MPCD_G float* const r = ox + j * 6;
+                *(MPCD_G Rec4*)r = Rec4{qx[u], qy[u], qz[u], ux[u]};
+                *(MPCD_G Rec2*)(r + 4) = Rec2{uy[u], uz[u]};
             }
-            ox[j] = px;
-            oy[j] = py;
-            oz[j] = pz;
-            ovx[j] = ux[u];
-            ovy[j] = uy[u];
-            ovz[j] = uz[u];
             if (oid) oid[j] = id[u];
             if (has_m) gp(b.m[dst])[j] = gp(b.m[src])[i];
+        }
+    }
+}
+
+// Re-bucketing, after k_scatter: its records of six floats become the arrays
+// of the current buffer again, up to the overflow bucket.  A fresh box's
+// particles are in random order, so each store of the scatter is a line of its
+// own; a record takes two (and an id or mass one more) where the six arrays
+// took six: 32 boxes of 30 M particles with ids 3.18 ms before, 1.55 and 0.43
+// now; the first 40 steps of a 256^3 box 122 -> 102 ms.  The records lie over
+// the idle buffer's six arrays, which are one stretch of memory.
+__global__ __launch_bounds__(kBlock) void k_unpack(const Tile* __restrict__ tiles,
+                                                    const BoxDev* __restrict__ boxes,
+                                                    const BoxState* __restrict__ st)
+{
+    const Tile tl = tiles[xcd_tile(blockIdx.x, gridDim.x)];
+    const BoxState s = st[uniform(tl.box)];
+    const BoxDev& b = boxes[uniform(tl.box)];
+    if (b.binning != 1 || box_idle(s) || !s.rebucket) return;
+    const int par = uniform(s.parity), from = par ^ 1;
+    const MPCD_G float* const rec = ugp(b.p[from][0]);
+    MPCD_G float* out[6];
+#pragma unroll
+    for (int d = 0; d < 6; ++d) out[d] = ugp(b.p[par][d]);
+    const bool has_id = b.pid[par] != nullptr, has_m = b.m[par] != nullptr;
+    const int64_t end = min(tl.end, (int64_t)b.bstart[b.nbrick]);
+    constexpr int kU = 4;
+    for (int64_t i0 = tl.begin + threadIdx.x; i0 < end; i0 += (int64_t)kBlock * kU) {
+        Rec4 a[kU];
+        Rec2 c[kU];
+        int32_t id[kU];
+        float m[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int64_t i = i0 + (int64_t)u * kBlock, j = i < end ? i : tl.begin;
+            a[u] = *(const MPCD_G Rec4*)(rec + j * 6);
+            c[u] = *(const MPCD_G Rec2*)(rec + j * 6 + 4);
+            id[u] = has_id ? gp(b.pid[from])[j] : 0;
+            m[u] = has_m ? gp(b.m[from])[j] : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int64_t i = i0 + (int64_t)u * kBlock;
+            if (i >= end) break;
+            out[0][i] = a[u].x;
+            out[1][i] = a[u].y;
+            out[2][i] = a[u].z;
+            out[3][i] = a[u].w;
+            out[4][i] = c[u].x;
+            out[5][i] = c[u].y;
+            if (has_id) gp(b.pid[par])[i] = id[u];
+            if (has_m) gp(b.m[par])[i] = m[u];
         }
     }
 }
@@ -1358,7 +1415,7 @@ __global__ void k_flip(const int32_t* __restrict__ active, int nactive,
     const int bx = active[i];
     BoxState& s = st[bx];
     const bool due = !box_idle(s) && sort_due(boxes[bx], s);
-    if (due) s.parity ^= 1;
+    if (due && boxes[bx].binning == 2) s.parity ^= 1;   // (a re-bucketed box stays in its buffer)
     if (due && boxes[bx].binning == 1) s.rebuckets += 1;
     s.rebucket = 0;
 }
@@ -2397,6 +2454,10 @@ void launch_scan(const Tables& T, hipStream_t s)
 void launch_scatter(const Tables& T, hipStream_t s)
 {
     MPCD_LAUNCH(k_scatter, T.nptiles, kBlock, s, T.ptiles, T.boxes, T.state);
+}
+void launch_unpack(const Tables& T, hipStream_t s)
+{
+    MPCD_LAUNCH(k_unpack, T.nptiles, kBlock, s, T.ptiles, T.boxes, T.state);
 }
 void launch_flip(const Tables& T, hipStream_t s)
 {

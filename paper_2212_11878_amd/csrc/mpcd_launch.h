@@ -46,6 +46,7 @@ void launch_zero_counts(const Tables& T, hipStream_t s);
 void launch_count(const Tables& T, hipStream_t s);
 void launch_scan(const Tables& T, hipStream_t s);
 void launch_scatter(const Tables& T, hipStream_t s);
+void launch_unpack(const Tables& T, hipStream_t s);
 void launch_flip(const Tables& T, hipStream_t s);
 void launch_cell_rotate(const Tables& T, hipStream_t s);
 

@@ -227,3 +227,34 @@ def test_sort_sums_beyond_their_fast_range(mp, scale, density):
             ctx.step(3)
             out.append(ctx.get_state(slot))
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("n", [1, 4095, 4097, 70001])
+@pytest.mark.parametrize("more", [{}, dict(unordered=True), dict(particle_mass=True)])
+def test_bucketed_state_is_the_state(mp, n, more):
+    """Bucketing moves whole particles, ids and masses with them, from either
+    buffer: the observables of a step, and the state by id, are those of
+    counting-sort binning."""
+    from gpu_util import same_particle_set
+    L = (19, 8, 13)
+    pos, vel = inputs.thermal_state(L, n, seed=n)
+    mass = np.random.default_rng(n).uniform(0.5, 2.0, n).astype(np.float32)
+    out = []
+    for binning in (mp.MPCD_BIN_ATOMIC, mp.MPCD_BIN_SORT):
+        with mp.Context(binning=binning, brick=4) as ctx:
+            slot = ctx.admit(mp.make_desc(L, n, init="external", seed=3, **more))
+            seen = []
+            for steps in (1, 2):
+                ctx.set_state(slot, (pos, vel), 5)
+                if "particle_mass" in more:
+                    ctx.set_mass(slot, mass)
+                ctx.step(steps)
+                obs = ctx.observe(slot)
+                seen.append((obs["E"], tuple(obs["P"]), ctx.get_state(slot)))
+            out.append(seen)
+    for a, b in zip(*out):
+        assert a[:2] == b[:2]
+        if "unordered" in more:
+            assert same_particle_set(a[2][0], a[2][1], b[2][0], b[2][1])
+        else:
+            assert np.array_equal(a[2][0], b[2][0]) and np.array_equal(a[2][1], b[2][1])
