@@ -448,6 +448,21 @@ __host__ __device__ __forceinline__ uint32_t isqrt_ceil(uint32_t n)
     return r;
 }
 
+// Runs of tiles that the first level of k_box_stats folds, each into a 128-bit
+// record over its first two tiles' partials: at most kBlock runs of `per` tiles,
+// the last one up to 2 per - 1, so that no run has fewer than two (a last run
+// of one tile would put half of its record beyond the partials).
+struct StatRuns {
+    int ntile, per, groups;
+    __host__ __device__ int begin(int g) const { return g * per; }
+    __host__ __device__ int end(int g) const { return g == groups - 1 ? ntile : (g + 1) * per; }
+};
+__host__ __device__ __forceinline__ StatRuns stat_runs(int ntile)
+{
+    const int per = (ntile + kBlock - 1) / kBlock, p = per < 2 ? 2 : per;
+    return StatRuns{ntile, p, ntile < 2 * p ? 1 : ntile / p};
+}
+
 // Spare slots given to a bucket that re-bucketing found holding n
 // particles: the bucket's size wanders like a Poisson count, so the margin
 // is about 4 standard deviations plus 1/8 and a constant.

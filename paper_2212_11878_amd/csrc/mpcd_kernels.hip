@@ -2214,12 +2214,11 @@ __global__ __launch_bounds__(kStatBlock) void k_box_stats(const long long* __res
 }
 
 // First level of k_box_stats for boxes with many tiles: workgroup g sums the
-// partials of tiles [g per, (g + 1) per) and stores the 128-bit totals over
-// the first two tiles of its run (per >= 2; each workgroup reads and writes
-// only its own run).
-__global__ __launch_bounds__(kStatBlock) void k_box_stats_tiles(long long* __restrict__ partials, int ntiles, int per)
+// partials of the tiles of run g and stores the 128-bit totals over the first
+// two of them (each workgroup reads and writes only its own run).
+__global__ __launch_bounds__(kStatBlock) void k_box_stats_tiles(long long* __restrict__ partials, StatRuns runs)
 {
-    const int t0 = blockIdx.x * per, t1 = min(ntiles, t0 + per);
+    const int t0 = runs.begin((int)blockIdx.x), t1 = runs.end((int)blockIdx.x);
     __int128 tot[kNumDiag];
     long long hi;
     unsigned long long lo;
@@ -2491,10 +2490,9 @@ void launch_box_stats(const Tables& T, int32_t box, int ntile, long long* part, 
                            T.state + box, mode, kT, mass, report);
         return;
     }
-    const int per = (ntile + kBlock - 1) / kBlock;   // >= 5, so each run holds two tiles' slots
-    const int groups = (ntile + per - 1) / per;
-    hipLaunchKernelGGL(k_box_stats_tiles, dim3(groups), dim3(kStatBlock), 0, s, part, ntile, per);
-    hipLaunchKernelGGL(k_box_stats, dim3(1), dim3(kStatBlock), 0, s, part, groups, per, 1, T.boxes + box,
+    const StatRuns runs = stat_runs(ntile);
+    hipLaunchKernelGGL(k_box_stats_tiles, dim3(runs.groups), dim3(kStatBlock), 0, s, part, runs);
+    hipLaunchKernelGGL(k_box_stats, dim3(1), dim3(kStatBlock), 0, s, part, runs.groups, runs.per, 1, T.boxes + box,
                        T.state + box, mode, kT, mass, report);
 }
 void launch_mark_holes_box(const Tables& T, int32_t box, int ntile, hipStream_t s)

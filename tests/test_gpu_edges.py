@@ -258,3 +258,22 @@ def test_bucketed_state_is_the_state(mp, n, more):
             assert same_particle_set(a[2][0], a[2][1], b[2][0], b[2][1])
         else:
             assert np.array_equal(a[2][0], b[2][0]) and np.array_equal(a[2][1], b[2][1])
+
+
+@pytest.mark.parametrize("tiles", [1025, 1026, 1030, 1281])
+def test_observing_a_large_box_leaves_its_neighbours_alone(mp, tiles):
+    """Tile counts whose last run of the first reduction level would hold one
+    tile: the record of its sums stays inside the box's own memory."""
+    n = 4096 * tiles
+    small = mp.make_desc((10, 9, 8), 7000, seed=5)
+    with mp.Context(binning=mp.MPCD_BIN_SORT) as ctx, mp.Context(binning=mp.MPCD_BIN_SORT) as alone:
+        big = ctx.admit(mp.make_desc((128, 128, 64), n, seed=2, unordered=True))
+        slots = [ctx.admit(small) for _ in range(4)]
+        one = alone.admit(small)
+        for _ in range(3):
+            ctx.step(1)
+            alone.step(1)
+            assert abs(ctx.observe(big)["T"] - 1.0) < 1e-6
+        _, want_v, _ = alone.get_state(one)
+        for slot in slots:
+            assert np.array_equal(ctx.get_state(slot)[1], want_v)
