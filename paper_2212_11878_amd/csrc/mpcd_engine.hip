@@ -503,13 +503,15 @@ int enqueue_step(mpcd_ctx* c, bool with_sort)
         if (rc) return rc;                                     \
     } while (0)
     if (c->any_sort || with_sort) {
-        if (with_sort && c->any_brick) {
+        // (a context that holds both forms sorts every step, and a brick box
+        // flagged by the step before takes part without the host)
+        if (c->any_brick) {
             STEP_K(K_MARK, launch_mark_holes(T.ptiles, T.nptiles, T, 0, s); launch_rebucket_clear(T, s));
         }
         STEP_K(K_ZERO, launch_zero_counts(T, s));
         STEP_K(K_COUNT, launch_count(T, s));
         STEP_K(K_SCAN, launch_scan(T, s));
-        STEP_K(K_SCATTER, launch_scatter(T, s); if (with_sort && c->any_brick) launch_unpack(T, s));
+        STEP_K(K_SCATTER, launch_scatter(T, s); if (c->any_brick) launch_unpack(T, s));
         STEP_K(K_FLIP, launch_flip(T, s));
     }
     if (c->any_brick) STEP_K(K_BRICK_STEP, launch_brick_step(T, s));
