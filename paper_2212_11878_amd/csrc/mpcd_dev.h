@@ -821,8 +821,7 @@ __device__ __forceinline__ void am_moments(double mj, float vx, float vy, float 
 }
 
 // The same terms 1 .. 12 for mass 1, as FP64 integers below 2^40 (a <= 16,
-// velocities below the limit), so that sums of fewer than kMaxCellCount terms
-// are exact.
+// velocities below the limit), so that sums of up to 2^13 terms are exact.
 __device__ __forceinline__ void am_moments_exact(float vx, float vy, float vz, const double r[3], double t[kAmMoments])
 {
 #pragma clang fp contract(off)
@@ -893,11 +892,13 @@ __device__ __forceinline__ bool am_dl(double mj, float vx, float vy, float vz, c
 #pragma unroll
     for (int e = 0; e < 3; ++e) {
         // rounded to an integer by adding 1.5 2^52, whose low bits then hold
-        // it (below 2^51 in magnitude; larger terms are refused)
+        // it (below 2^51 in magnitude; terms that are refused are clamped)
         const double y = l[e] * 4294967296.0 + kRoundMagic;
         t[e] = __double_as_longlong(y) - (long long)kRoundBits;
         ok = ok && fabs(y - kRoundMagic) < 281474976710656.0;   // 2^48
     }
+    if (!ok)
+        for (int e = 0; e < 3; ++e) t[e] = fixed_term(l[e]);
     return ok;
 }
 

@@ -149,7 +149,7 @@ __device__ __forceinline__ void step_flush(const long long (&d)[kNumDiag], bool 
 
 // The same without a workgroup barrier: each wave adds its own share of the
 // VACF sum (at most 4096 terms below 3 2^48) and its range-violation mark.
-__device__ __forceinline__ void step_flush_wave(long long viol, long long vsum, bool vacf, long long* acc,
+__device__ __forceinline__ void step_flush_wave(uint32_t viol, long long vsum, bool vacf, long long* acc,
                                                 int lane_sel)
 {
     long long* a = acc + (size_t)(lane_sel & (kAccLanes - 1)) * 3;
@@ -161,7 +161,7 @@ __device__ __forceinline__ void step_flush_wave(long long viol, long long vsum, 
             gatomic_add(gp(a) + 1, (long long)(unsigned long long)(unsigned)(v & 0xffffffffll));
         }
     }
-    if (__any(viol != 0) && lane == 0) gatomic_add(gp(a) + 2, 1ll);
+    if (__any(viol != 0u) && lane == 0) gatomic_add(gp(a) + 2, 1ll);
 }
 
 // Block-wide exclusive scan of one uint32 per thread; returns the prefix and
@@ -322,15 +322,17 @@ __device__ __forceinline__ bool inside(float x, float len)
 }
 
 // Term of an exact cell sum held in FP64: v 2^32 truncated toward zero, the
-// value of to_fixed(v).  Below the velocity limit a term is an integer below
-// 2^40 and a cell of fewer than kMaxCellCount terms sums to less than 2^52, so
-// FP64 additions are exact in any order and give the integer sum.  (The clamp
-// keeps a velocity that is not finite out of the cell's sum; its box is
-// marked.)
+// value of to_fixed(v) for velocities in range.  It is an integer below 2^40,
+// so FP64 additions of up to kExactCount of them are exact in any order and
+// give the integer sum.  Boxes with a velocity out of range are marked
+// (BoxState::status, by the call that set the state or the step that made the
+// velocity): their cells, and larger ones, are summed in 64-bit integers, as
+// counting-sort binning and the CPU leg do.
+constexpr uint32_t kExactCount = 8192u;
 __device__ __forceinline__ double exact_term(float v)
 {
-    constexpr float kQ = 4294967296.0f, kTop = kVelocityLimit * kQ;
-    return (double)truncf(__builtin_amdgcn_fmed3f(v * kQ, -kTop, kTop));
+    constexpr float kQ = 4294967296.0f;
+    return (double)truncf(v * kQ);
 }
 
 // One SRD step of one brick (paper Sec. 2; the shifted grid of Sec. 3.1;
@@ -359,13 +361,14 @@ __device__ __forceinline__ double exact_term(float v)
 // The instance for equal masses without particle ids is held to 5 waves per
 // SIMD (96 registers), those with ids or 8 slots per thread to 4.
 // Angular-momentum rule: one particle's terms of the first pass into its
-// cell's record.  Equal masses: the twelve sums are held in FP64 (rounded to
-// integers below 2^40, so additions are exact in any order, as in exact_term,
-// and no 64-bit conversion is needed); per-particle masses in 64-bit integers.
-__device__ __forceinline__ void am_add(unsigned long long* ra, bool has_mass, float m, float vx, float vy, float vz,
+// cell's record, as 64-bit integers (`ints`: per-particle masses, and where
+// exact_term does not hold) or, for mass 1, in FP64 (rounded to integers below
+// 2^40, so additions are exact in any order, as in exact_term, and no 64-bit
+// conversion is needed).
+__device__ __forceinline__ void am_add(unsigned long long* ra, bool ints, float m, float vx, float vy, float vz,
                                        const double rl[3])
 {
-    if (has_mass) {
+    if (ints) {
         long long tm[kAmMoments];
         am_moments((double)m, vx, vy, vz, rl, tm);
 #pragma unroll
@@ -402,8 +405,8 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
                   const BoxState* __restrict__ st, long long* __restrict__ dacc)
 {
     // LDS, per cell of the brick: exact sums of m v and of m in 40-byte
-    // records (equal masses: three FP64 sums and a 32-bit count; per-particle
-    // masses: four 64-bit integers and a count), then the collision map in
+    // records (equal masses: three FP64 sums, or integers, and a 32-bit count;
+    // per-particle masses: four 64-bit integers and a count), then the collision map in
     // 48-byte records (three 16-byte reads); both strides spread neighbouring
     // cells over the LDS banks.  Boxes with the angular-momentum rule (kAM
     // instances only) use kAmWords per cell instead.
@@ -468,7 +471,7 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
 
     float px[kS], py[kS], pz[kS], vx[kS], vy[kS], vz[kS], pm[kMass ? kS : 1];
     uint32_t meta[kS];   // cell in the brick after loading; destination group << 24 | rank later
-    long long viol = 0;
+    uint32_t viol = 0u;
     auto mass_at = [&](int u) -> float { return kMass ? pick(pm, u) : 1.0f; };
     // slots of chunk ch that hold particles for some thread (uniform)
     auto used_slots = [&](int ch) -> int {
@@ -527,7 +530,7 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
             put(py, u, y);
             put(pz, u, z);
             put(meta, u, in ? (uint32_t)(cx + ex * (cy + ey * cz)) : kNone);
-            if (!in) viol += 1;
+            if (!in) viol = 1u;
         }
     };
 
@@ -564,17 +567,18 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
     if (threadIdx.x < 27 + kWaves) gcnt[threadIdx.x] = 0u;
     __syncthreads();
     const bool flagged = eflag_k == stamp;
-    const uint32_t L0 = (uint32_t)b.L[0], L01 = (uint32_t)b.L[0] * (uint32_t)b.L[1];
-    // Angular-momentum rule, flagged brick: the particles of this step's
-    // overflow bucket whose collision cell lies here are read directly (pass
-    // 1: moments, pass 2: angular-momentum change), as their escape sums
-    // carry no moments.
-    auto am_overflow = [&](int pass) {
-        const uint32_t nbk = (uint32_t)b.nbrick;
-        const uint32_t ob = gp(b.bstart)[nbk];
-        const uint32_t ocnt = min(gp(b.bsize[src])[nbk], gp(b.bstart)[nbk + 1] - ob);
-        for (uint32_t q = threadIdx.x; q < ocnt; q += kT) {
-            const uint32_t si = ob + q;
+    const uint32_t nbk = (uint32_t)b.nbrick;
+    auto overflow_count = [&]() {
+        return min(gp(b.bsize[src])[nbk], gp(b.bstart)[nbk + 1] - gp(b.bstart)[nbk]);
+    };
+    const bool fp64 = (kAM && am) ? !has_mass : !kMass;   // equal masses
+    // From memory: the particles of the slots [first, first + n) whose collision
+    // cell lies in this brick.  Pass 1 sums (plain rule: integers; `ints` as in
+    // am_add), pass 2 adds their angular-momentum change.
+    auto add_slots = [&](uint32_t first, uint32_t n, int pass, bool ints) {
+#pragma unroll 1
+        for (uint32_t q = threadIdx.x; q < n; q += kT) {
+            const uint32_t si = first + q;
             const float ux = gp(b.p[src][3])[si], uy = gp(b.p[src][4])[si], uz = gp(b.p[src][5])[si];
             const float qx = fold(fmaf(ux, dt, gp(b.p[src][0])[si]), b.len[0]);
             const float qy = fold(fmaf(uy, dt, gp(b.p[src][1])[si]), b.len[1]);
@@ -584,47 +588,97 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
             const int cz = axis_cell(qz, sh.z, inv_a, b.L[2]) - loz;
             if ((unsigned)cx >= (unsigned)ex || (unsigned)cy >= (unsigned)ey || (unsigned)cz >= (unsigned)ez) continue;
             const int c = cx + ex * (cy + ey * cz);
-            const float mj = has_mass ? gp(b.m[src])[si] : 1.0f;
-            double rl[3];
-            am_local(b.a, qx, qy, qz, sh, rl);
-            unsigned long long* const ra = acc + c * kAmWords;
-            if (pass == 1) am_add(ra, has_mass, mj, ux, uy, uz, rl);
-            else if (!am_add_dl(ra, mj, ux, uy, uz, rl, b.ca, b.sa)) viol += 1;
-        }
-    };
-    if (flagged) {   // overflow particles of this step whose cells lie here
-        MPCD_G CellAcc* __restrict__ esc = gp(b.esc[k & 1]);
-        for (int c = threadIdx.x; c < ncl; c += kT) {
-            const int lx = c % ex, ly = (c / ex) % ey, lz = c / (ex * ey);
-            const uint32_t gc = (uint32_t)(lox + lx) + L0 * (uint32_t)(loy + ly) + L01 * (uint32_t)(loz + lz);
-            const CellAcc e = load_acc(esc + gc);
-            if (e.w) {
+            if (kAM && am) {
+                const float mj = has_mass ? gp(b.m[src])[si] : 1.0f;
+                double rl[3];
+                am_local(b.a, qx, qy, qz, sh, rl);
+                unsigned long long* const ra = acc + c * kAmWords;
+                if (pass == 1) am_add(ra, ints, mj, ux, uy, uz, rl);
+                else if (!am_add_dl(ra, mj, ux, uy, uz, rl, b.ca, b.sa)) viol = 1u;
+            } else {
                 unsigned long long* const r = acc + c * kAccWords;
-                if (kAM && am) {
-                    // the particles themselves are read below
-                } else if (kMass) {
-                    r[0] += e.sx;
-                    r[1] += e.sy;
-                    r[2] += e.sz;
-                    r[3] += e.w;
-                    if (has_mass) {   // and their count
-                        MPCD_G uint32_t* const ec = gp(b.ecnt[k & 1]) + gc;
-                        *reinterpret_cast<uint32_t*>(&r[4]) += *ec;
-                        *ec = 0u;
-                    }
-                } else {
-                    double* const rd = reinterpret_cast<double*>(r);
-                    rd[0] += fixed_to_double(e.sx);   // integers below 2^52: exact
-                    rd[1] += fixed_to_double(e.sy);
-                    rd[2] += fixed_to_double(e.sz);
-                    r[3] += e.w >> 32;   // escape weights are 2^32 m
-                }
-                CellAcc z = {0ull, 0ull, 0ull, 0ull};
-                store_acc(esc + gc, z);
+                atomicAdd(&r[0], to_fixed(ux));
+                atomicAdd(&r[1], to_fixed(uy));
+                atomicAdd(&r[2], to_fixed(uz));
+                atomicAdd(reinterpret_cast<uint32_t*>(&r[3]), 1u);
             }
         }
-        if (kAM && am) am_overflow(1);
+    };
+    const uint32_t L0 = (uint32_t)b.L[0], L01 = (uint32_t)b.L[0] * (uint32_t)b.L[1];
+    // The rare cases: overflow particles of this step whose cells lie here, and
+    // equal masses whose sums FP64 may not hold (exact_term), which are taken
+    // once more in integers and then rounded to FP64 as sums of masses are.
+    if (flagged || (fp64 && (s.status != 0 || cnt > kExactCount))) {
+        bool ints = !fp64;
+        if (fp64) {
+            bool again = s.status != 0 || (flagged && cnt + overflow_count() > kExactCount);
+            if (!again && cnt > kExactCount) {   // a crowded cell?
+                if (threadIdx.x == 0) gslot[0].x = 0u;   // (free until the groups reserve)
+                __syncthreads();
+                for (int c = threadIdx.x; c < ncl; c += kT)
+                    if ((kAM && am ? acc[c * kAmWords + kAmMoments] : acc[c * kAccWords + 3]) > kExactCount)
+                        gslot[0].x = 1u;
+                __syncthreads();
+                again = gslot[0].x != 0u;
+            }
+            if (again) {
+                ints = true;
+                for (int i = threadIdx.x; i < (am ? kAmWords : kAccWords) * ncl; i += kT) lds64[i] = 0ull;
+                __syncthreads();
+                add_slots(beg, cnt, 1, true);
+                __syncthreads();
+            }
+        }
+        if (flagged) {
+            MPCD_G CellAcc* __restrict__ esc = gp(b.esc[k & 1]);
+            for (int c = threadIdx.x; c < ncl; c += kT) {
+                const int lx = c % ex, ly = (c / ex) % ey, lz = c / (ex * ey);
+                const uint32_t gc = (uint32_t)(lox + lx) + L0 * (uint32_t)(loy + ly) + L01 * (uint32_t)(loz + lz);
+                const CellAcc e = load_acc(esc + gc);
+                if (e.w) {
+                    unsigned long long* const r = acc + c * kAccWords;
+                    if (kAM && am) {
+                        // their escape sums carry no moments: the particles
+                        // themselves are read below
+                    } else if (kMass) {
+                        r[0] += e.sx;
+                        r[1] += e.sy;
+                        r[2] += e.sz;
+                        r[3] += e.w;
+                        if (has_mass) {   // and their count
+                            MPCD_G uint32_t* const ec = gp(b.ecnt[k & 1]) + gc;
+                            *reinterpret_cast<uint32_t*>(&r[4]) += *ec;
+                            *ec = 0u;
+                        }
+                    } else {
+                        double* const rd = reinterpret_cast<double*>(r);
+                        if (ints) {
+                            r[0] += e.sx;
+                            r[1] += e.sy;
+                            r[2] += e.sz;
+                        } else {
+                            rd[0] += fixed_to_double(e.sx);   // integers up to 2^53: exact
+                            rd[1] += fixed_to_double(e.sy);
+                            rd[2] += fixed_to_double(e.sz);
+                        }
+                        r[3] += e.w >> 32;   // escape weights are 2^32 m
+                    }
+                    CellAcc z = {0ull, 0ull, 0ull, 0ull};
+                    store_acc(esc + gc, z);
+                }
+            }
+            if (kAM && am) add_slots(gp(b.bstart)[nbk], overflow_count(), 1, ints);
+        }
         __syncthreads();
+        if (fp64 && ints) {
+            for (int c = threadIdx.x; c < ncl; c += kT) {
+                unsigned long long* const r = acc + c * (kAM && am ? kAmWords : kAccWords);
+                double* const rd = reinterpret_cast<double*>(r);
+#pragma unroll 1
+                for (int e = kAM && am ? 1 : 0; e < (kAM && am ? kAmMoments : 3); ++e) rd[e] = fixed_to_double(r[e]);
+            }
+            __syncthreads();
+        }
     }
 
     // 2. cell velocity and axis.  A brick has fewer cells than the workgroup
@@ -637,7 +691,7 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
         for (int c = tcell; c < ncl; c += kT) {
             unsigned long long* const ra = acc + c * kAmWords;
             if (ra[kAmMoments] == 0) continue;
-            if (ra[kAmMoments] >= kMaxCellCount) viol += 1;   // the cell's sums may have wrapped
+            if (ra[kAmMoments] >= kMaxCellCount) viol = 1u;   // the cell's sums may have wrapped
             const int lx = c % ex, ly = (c / ex) % ey, lz = c / (ex * ey);
             const uint32_t gc = (uint32_t)(lox + lx) + L0 * (uint32_t)(loy + ly) + L01 * (uint32_t)(loz + lz);
             double* const rec = reinterpret_cast<double*>(ra);
@@ -663,10 +717,10 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
                 if (c == kNone) continue;
                 double rl[3];
                 am_local(b.a, px[u], py[u], pz[u], sh, rl);
-                if (!am_add_dl(acc + c * kAmWords, kMass ? pm[u] : 1.0f, vx[u], vy[u], vz[u], rl, b.ca, b.sa)) viol += 1;
+                if (!am_add_dl(acc + c * kAmWords, kMass ? pm[u] : 1.0f, vx[u], vy[u], vz[u], rl, b.ca, b.sa)) viol = 1u;
             }
         }
-        if (flagged) am_overflow(2);
+        if (flagged) add_slots(gp(b.bstart)[nbk], overflow_count(), 2, false);
         __syncthreads();
         // 2c. per cell: omega (in place of Q); flagged bricks publish the
         // cell data for the overflow particles
@@ -695,7 +749,7 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
         const unsigned long long w = kMass ? r[3] : ((r[3] & 0xffffffffull) << 32);
         if (w == 0) continue;
         const uint32_t count = kMass ? (uint32_t)r[4] : (uint32_t)r[3];
-        if (count >= kMaxCellCount) viol += 1;   // the cell's sums may have wrapped
+        if (count >= kMaxCellCount) viol = 1u;   // the cell's sums may have wrapped
         const int lx = c % ex, ly = (c / ex) % ey, lz = c / (ex * ey);
         const uint32_t gc = (uint32_t)(lox + lx) + L0 * (uint32_t)(loy + ly) + L01 * (uint32_t)(loz + lz);
         double uc[3];
@@ -803,12 +857,12 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
             nstay += (uint32_t)__popcll(mask);
         }
         if (lane == 0) gcnt[27u + wave] = nstay;
-        if (!(vmax < kVelocityLimit)) viol += 1;
+        if (!(vmax < kVelocityLimit)) viol = 1u;
         while (redo) {   // periodic images and far destinations, in the exact general form
             const int u = __ffs((int)redo) - 1;
             redo &= redo - 1u;
             const float3 v = make_float3(pick(vx, u), pick(vy, u), pick(vz, u));
-            if (!in_range(v)) viol += 1;
+            if (!in_range(v)) viol = 1u;
             const float qx = fold(fmaf(v.x, dt, pick(px, u)), len0);
             const float qy = fold(fmaf(v.y, dt, pick(py, u)), len1);
             const float qz = fold(fmaf(v.z, dt, pick(pz, u)), len2);
@@ -907,7 +961,7 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
                 placed = place_single(b, dst, (uint32_t)(db.x + nb0 * (db.y + nb1 * db.z)), &j);
             if (!placed) placed = place_overflow(b, dst, k, nc, m, v, &j);
             if (placed) store_at(j, x, y, z, v, kIds ? pick(id, u) : 0, m);
-            else viol += 1;
+            else viol = 1u;
         }
         if (ch + 1 < nch) __syncthreads();
     }

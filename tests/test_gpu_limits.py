@@ -1,0 +1,87 @@
+"""Boxes beyond the ranges that the exact sums are made for."""
+import numpy as np
+import pytest
+
+from paper_2212_11878_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mp():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2212_11878_amd import mpcd
+    return mpcd
+
+
+def _with_fast(vel, speed, count, seed):
+    """`count` of the particles get components of magnitude speed / 2 to speed."""
+    g = np.random.default_rng(seed)
+    i = g.choice(vel.shape[1], count, replace=False)
+    vel[:, i] = (g.uniform(0.5, 1.0, (3, count)) * speed * g.choice([-1.0, 1.0], (3, count))).astype(np.float32)
+    return vel
+
+
+@pytest.mark.parametrize("speed", [300.0, 5e4, 3e9, 3e38])
+@pytest.mark.parametrize("more", [{}, dict(unordered=True), dict(conserve_l=True), dict(particle_mass=True)])
+def test_velocities_out_of_range_equal_sort(mp, speed, more):
+    """A box with velocities beyond the limit (256) is marked, and still
+    steps to the bits of counting-sort binning: both sum the same integers."""
+    from gpu_util import same_particle_set
+    L, n = (12, 9, 10), 10800
+    pos, vel = inputs.thermal_state(L, n, seed=6)
+    vel = _with_fast(vel, speed, 40, 7)
+    out = []
+    for binning in (mp.MPCD_BIN_ATOMIC, mp.MPCD_BIN_SORT):
+        with mp.Context(binning=binning, brick=4) as ctx:
+            slot = ctx.admit(mp.make_desc(L, n, init="external", seed=3, **more), (pos, vel))
+            ctx.step(3)
+            out.append(ctx.get_state(slot))
+            assert ctx.observe(slot)["status"] == mp.MPCD_ESTATE
+    if "unordered" in more and speed < 1e38:
+        assert same_particle_set(out[0][0], out[0][1], out[1][0], out[1][1])
+    elif "unordered" not in more:
+        assert np.array_equal(out[0][0], out[1][0], equal_nan=True)
+        assert np.array_equal(out[0][1], out[1][1], equal_nan=True)
+
+
+@pytest.mark.parametrize("more", [{}, dict(conserve_l=True), dict(particle_mass=True)])
+def test_velocities_out_of_range_through_overflow(mp, more):
+    """The same while buckets overflow: escape sums carry the fast particles' terms."""
+    L, n = (16, 16, 16), 20000
+    g = np.random.default_rng(31)
+    pos = (g.uniform(0.0, 1.0, (3, n)) * np.array([[3.0], [16.0], [16.0]])).astype(np.float32)
+    vel = g.standard_normal((3, n)).astype(np.float32)
+    vel[0] += np.float32(4.0)
+    vel = _with_fast(vel, 900.0, 300, 8)
+    out, obs = [], []
+    for binning in (mp.MPCD_BIN_ATOMIC, mp.MPCD_BIN_SORT):
+        with mp.Context(binning=binning, brick=4) as ctx:
+            slot = ctx.admit(mp.make_desc(L, n, init="external", seed=3, **more), (pos, vel))
+            for _ in range(4):
+                ctx.step(3)
+            out.append(ctx.get_state(slot))
+            obs.append(ctx.observe(slot))
+    assert obs[0]["overflow_steps"] > 0 and obs[0]["status"] == mp.MPCD_ESTATE
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+    assert obs[0]["E"] == obs[1]["E"] and np.array_equal(obs[0]["P"], obs[1]["P"])
+
+
+@pytest.mark.parametrize("cells,count", [(1, 5000), (1, 100000), (8, 40000)])
+def test_crowded_cells_at_high_speed_equal_sort(mp, cells, count):
+    """More particles in a cell than the exact range allows (4096), near the
+    velocity limit: the box is marked, the bits are those of counting-sort binning."""
+    L = {1: (1, 1, 1), 8: (2, 2, 2)}[cells]
+    g = np.random.default_rng(count)
+    pos = (g.uniform(0.0, 0.999, (3, count)) * np.array(L)[:, None]).astype(np.float32)
+    vel = g.uniform(200.0, 255.0, (3, count)).astype(np.float32)
+    out = []
+    for binning in (mp.MPCD_BIN_ATOMIC, mp.MPCD_BIN_SORT):
+        with mp.Context(binning=binning) as ctx:
+            slot = ctx.admit(mp.make_desc(L, count, init="external", seed=3, dt=0.01), (pos, vel))
+            ctx.step(2)
+            out.append(ctx.get_state(slot))
+            assert ctx.observe(slot)["status"] == mp.MPCD_ESTATE
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
