@@ -121,47 +121,27 @@ __device__ __forceinline__ void block_diag(long long (&d)[kNumDiag], long long* 
     }
 }
 
-// End of a step kernel's workgroup: add its exact VACF partial (on sampled
-// steps) and a range-violation mark to the box's accumulators.  Atomic
-// integer adds are exact, so the order does not matter; the workgroups are
-// spread over kAccLanes lanes per box (high and low 32-bit halves of the
-// VACF sum, so no lane can overflow).
-template <int kT = kBlock>
-__device__ __forceinline__ void step_flush(const long long (&d)[kNumDiag], bool vacf, long long* acc, int lane_sel)
+// A wave's share of the box's VACF sum, at most 8192 terms below 3 2^48, into
+// the box's accumulators: high and low 32-bit halves, so no lane can overflow.
+// Atomic integer adds are exact, so the order does not matter; the workgroups
+// are spread over kAccLanes lanes per box.
+__device__ __forceinline__ void vacf_flush_wave(long long vsum, long long* acc, int lane_sel)
 {
-    __shared__ long long red[kT / kWave];
-    const int any = __syncthreads_or(d[5] != 0);
     long long* a = acc + (size_t)(lane_sel & (kAccLanes - 1)) * 3;
-    if (vacf) {
-        const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-        const long long v = wave_sum(d[4]);
-        if (lane == 0) red[w] = v;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            long long t = 0;
-            for (int i = 0; i < kT / kWave; ++i) t += red[i];
-            gatomic_add(gp(a), t >> 32);
-            gatomic_add(gp(a) + 1, (long long)(unsigned long long)(unsigned)(t & 0xffffffffll));
-        }
+    const long long v = wave_sum(vsum);
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        gatomic_add(gp(a), v >> 32);
+        gatomic_add(gp(a) + 1, (long long)(unsigned long long)(unsigned)(v & 0xffffffffll));
     }
-    if (any && threadIdx.x == 0) gatomic_add(gp(a) + 2, 1ll);
 }
 
-// The same without a workgroup barrier: each wave adds its own share of the
-// VACF sum (at most 4096 terms below 3 2^48) and its range-violation mark.
-__device__ __forceinline__ void step_flush_wave(uint32_t viol, long long vsum, bool vacf, long long* acc,
-                                                int lane_sel)
+// End of a wave of a step kernel: what is left of its VACF sum (on sampled
+// steps) and its range-violation mark.
+__device__ __forceinline__ void step_flush_wave(bool viol, long long vsum, bool vacf, long long* acc, int lane_sel)
 {
-    long long* a = acc + (size_t)(lane_sel & (kAccLanes - 1)) * 3;
-    const int lane = threadIdx.x & (kWave - 1);
-    if (vacf) {
-        const long long v = wave_sum(vsum);
-        if (lane == 0) {
-            gatomic_add(gp(a), v >> 32);
-            gatomic_add(gp(a) + 1, (long long)(unsigned long long)(unsigned)(v & 0xffffffffll));
-        }
-    }
-    if (__any(viol != 0u) && lane == 0) gatomic_add(gp(a) + 2, 1ll);
+    if (vacf) vacf_flush_wave(vsum, acc, lane_sel);
+    if (__any(viol) && (threadIdx.x & (kWave - 1)) == 0)
+        gatomic_add(gp(acc) + (size_t)(lane_sel & (kAccLanes - 1)) * 3 + 2, 1ll);
 }
 
 // Block-wide exclusive scan of one uint32 per thread; returns the prefix and
@@ -963,15 +943,23 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
             if (placed) store_at(j, x, y, z, v, kIds ? pick(id, u) : 0, m);
             else viol = 1u;
         }
-        if (ch + 1 < nch) __syncthreads();
+        if (ch + 1 < nch) {
+            if (kIds && vacf) {   // (a wave's chunk has at most 512 terms)
+                vacf_flush_wave(vsum, dacc + (size_t)uniform(tl.box) * kAccLanes * 3, blockIdx.x);
+                vsum = 0;
+            }
+            __syncthreads();
+        }
     }
-    step_flush_wave(viol, vsum, vacf, dacc + (size_t)uniform(tl.box) * kAccLanes * 3, blockIdx.x);
+    step_flush_wave(viol != 0u, vsum, vacf, dacc + (size_t)uniform(tl.box) * kAccLanes * 3, blockIdx.x);
 }
 
 // Particles of the overflow bucket of the current buffer (one workgroup per
 // box, after the brick step): the same step, with the cell data the flagged
-// bricks published.  Adds their diagnostics to d; returns their number.
-__device__ uint32_t overflow_step(const BoxDev& b, const BoxState& s, long long (&d)[kNumDiag])
+// bricks published.  Adds their diagnostics to d, the VACF terms to hi and lo
+// (as high and low words, so that any number fits); returns their number.
+__device__ uint32_t overflow_step(const BoxDev& b, const BoxState& s, long long (&d)[kNumDiag], long long& hi,
+                                  long long& lo)
 {
     const int src = s.parity, dst = s.parity ^ 1;
     const uint32_t nbk = (uint32_t)b.nbrick;
@@ -1009,7 +997,12 @@ __device__ uint32_t overflow_step(const BoxDev& b, const BoxState& s, long long 
             continue;
         }
         const int32_t id = b.pid[src] ? gp(b.pid[src])[si] : 0;
-        if (vacf) vacf_term(b, id, v, d);
+        if (vacf) {
+            d[4] = 0;
+            vacf_term(b, id, v, d);
+            hi += d[4] >> 32;
+            lo += (long long)(unsigned long long)(unsigned)(d[4] & 0xffffffffll);
+        }
         put_particle(b, dst, j, x, y, z, v, id, m, has_m);
     }
     return cnt;
@@ -1600,14 +1593,30 @@ void k_cell_rotate(const Tile* __restrict__ tiles, const BoxDev* __restrict__ bo
     const long long k = uniform(s.k);
     const bool vacf = vacf_due(b, s);
     long long d[kNumDiag] = {};
+    long long* const acc = dacc + (size_t)uniform(tl.box) * kAccLanes * 3;
     if (b.conserve_l) {
         const float3 sh = grid_shift(b, k);
+        long long hi = 0, lo = 0;
         for (int64_t c = tl.begin + threadIdx.x; c < tl.end; c += kBlock) {
             const uint32_t beg = b.cstart[c], end = b.cstart[c + 1];
             if (beg != end)
                 collide_cell_am(b, par, k, cell_of_key(b.L, b.sshift, (uint32_t)c), beg, end, sh, b.ca, b.sa, d, vacf);
+            if (vacf) {   // split after every cell (fewer than kMaxCellCount terms)
+                hi += d[4] >> 32;
+                lo += (long long)(unsigned long long)(unsigned)(d[4] & 0xffffffffll);
+                d[4] = 0;
+            }
         }
-        step_flush(d, vacf, dacc + (size_t)tl.box * kAccLanes * 3, blockIdx.x);
+        if (vacf) {
+            hi = wave_sum(hi);
+            lo = wave_sum(lo);
+            if ((threadIdx.x & (kWave - 1)) == 0) {
+                MPCD_G long long* const a = gp(acc) + (size_t)(blockIdx.x & (kAccLanes - 1)) * 3;
+                gatomic_add(a, hi);
+                gatomic_add(a + 1, lo);
+            }
+        }
+        step_flush_wave(d[5] != 0, 0, false, acc, blockIdx.x);
         return;
     }
     // the particles of the next buffer's slots come from the current buffer
@@ -1701,6 +1710,16 @@ void k_cell_rotate(const Tile* __restrict__ tiles, const BoxDev* __restrict__ bo
         gather(r.np);
     }
     if (fits(r2)) load_perm(r2.base, r2.np);
+    // A run leaves a wave kRotCap / 4 VACF terms, an oversized cell fewer than
+    // kMaxCellCount.
+    int runs = 0;
+    auto flush_runs = [&](int n) {
+        runs += n;
+        if (!vacf || runs < 16) return;
+        vacf_flush_wave(d[4], acc, blockIdx.x);
+        d[4] = 0;
+        runs = 0;
+    };
     while (r.c < nc) {
         const int c = r.c, e = r.e;
         const uint32_t base = r.base, np = r.np;
@@ -1722,6 +1741,7 @@ void k_cell_rotate(const Tile* __restrict__ tiles, const BoxDev* __restrict__ bo
             if (threadIdx.x == 0)
                 collide_cell_serial(b, par, k, cell_of_key(b.L, b.sshift, (uint32_t)(tl.begin + c)), base, cs[e], d,
                                     vacf);
+            flush_runs(16);
             r = r2;
             r2 = run_at(r.e);
             if (fits(r)) gather(r.np);
@@ -1823,10 +1843,11 @@ void k_cell_rotate(const Tile* __restrict__ tiles, const BoxDev* __restrict__ bo
             if (vacf) vacf_term(b, pid[base + j], v, d);
         }
         __syncthreads();   // the staging area is refilled by the next run
+        flush_runs(1);
         r = r2;
         r2 = r3;
     }
-    step_flush(d, vacf, dacc + (size_t)tl.box * kAccLanes * 3, blockIdx.x);
+    step_flush_wave(d[5] != 0, d[4], vacf, acc, blockIdx.x);
 }
 
 // --------------------------------------------------------------------------
@@ -1852,7 +1873,8 @@ __global__ __launch_bounds__(kBlock) void k_box_finish(const int32_t* __restrict
     uint32_t left = 0u;   // particles the step put into the overflow bucket
     if (!by_cell && threadIdx.x == 0) left = gp(b.bsize[sp->parity ^ 1])[b.nbrick];
     long long d[kNumDiag] = {};
-    const uint32_t drained = by_cell ? 0u : overflow_step(b, *sp, d);
+    long long hi = 0, lo = 0;   // VACF terms
+    const uint32_t drained = by_cell ? 0u : overflow_step(b, *sp, d, hi, lo);
     // the range check: this thread's particles and accumulator lane; on
     // sampled steps the VACF sum likewise, reduced over the workgroup
     const bool vac = vacf_due(b, *sp);
@@ -1861,7 +1883,6 @@ __global__ __launch_bounds__(kBlock) void k_box_finish(const int32_t* __restrict
     const bool out_of_range = __syncthreads_or(viol != 0) != 0;
     __shared__ long long red[2][kBlock / kWave];
     if (vac) {
-        long long hi = d[4] >> 32, lo = (long long)(unsigned long long)(unsigned)(d[4] & 0xffffffffll);
         if (threadIdx.x < kAccLanes) {
             hi += l[0];
             lo += l[1];

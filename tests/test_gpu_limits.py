@@ -1,4 +1,4 @@
-"""Boxes beyond the ranges that the exact sums are made for."""
+"""Boxes beyond the ranges that the exact sums are made for, and sums of many terms."""
 import numpy as np
 import pytest
 
@@ -85,3 +85,24 @@ def test_crowded_cells_at_high_speed_equal_sort(mp, cells, count):
             out.append(ctx.get_state(slot))
             assert ctx.observe(slot)["status"] == mp.MPCD_ESTATE
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("binning,brick,more", [
+    (1, (16, 8, 8), {}), (1, (16, 8, 8), dict(particle_mass=True)), (1, (8, 8, 8), dict(conserve_l=True)),
+    (2, 0, {}), (2, 0, dict(conserve_l=True))])
+def test_vacf_of_many_fast_particles(mp, binning, brick, more):
+    """One brick or cell tile holds 10^5 particles near the velocity limit
+    (200 a cell): its VACF sum leaves 64 bits, the sample may not.  All
+    velocities are equal, so the collision changes none beyond rounding (a few
+    parts in 10^7)."""
+    L, n, speed = (16, 8, 8), 204800, 254.0
+    g = np.random.default_rng(2)
+    pos = (g.uniform(0.0, 0.9999, (3, n)) * np.array(L)[:, None]).astype(np.float32)
+    vel = np.full((3, n), speed, np.float32)
+    with mp.Context(binning=binning, brick=brick) as ctx:
+        slot = ctx.admit(mp.make_desc(L, n, init="external", seed=3, dt=0.01, vacf_stride=1, **more), (pos, vel))
+        ctx.step(3)
+        obs = ctx.observe(slot)
+    print("[vacf]", obs["vacf"], flush=True)
+    assert len(obs["vacf"]) == 4
+    assert np.all(np.abs(obs["vacf"] - 3.0 * speed ** 2) <= 1e-5 * 3.0 * speed ** 2)
