@@ -208,9 +208,7 @@ int mpcd_admit(mpcd_ctx* ctx, const mpcd_box_desc* desc, int32_t* slot);
 /* Queue n_steps SRD steps (Sec. 2: streaming, random grid shift, cell
  * velocity, rotation about a random axis) for every live box whose step
  * budget is not exhausted; boxes that reach desc.n_steps stop advancing.
- * Asynchronous on the context stream (a call of a few steps, use_graph 1,
- * waits while four such calls before it are still queued).  EINVAL for
- * n_steps < 0. */
+ * Asynchronous on the context stream.  EINVAL for n_steps < 0. */
 int mpcd_step(mpcd_ctx* ctx, int32_t n_steps);
 
 /* Synchronise and read a box's diagnostics: total momentum and kinetic

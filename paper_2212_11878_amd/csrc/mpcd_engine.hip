@@ -45,11 +45,14 @@ const char* const kKernName[K_NUM] = {
 // a step) 14 to 18; 32 steps gain less than 1 % more.
 constexpr int kGraphSteps = 16;
 
-// Short calls (fewer than kGraphSteps steps) that may be queued at once.
-// Launched eagerly they cost the host less time than the GPU, and a host that
-// ran ahead without bound would learn of a full bucket (host_flag) only after
-// all it had queued.
-constexpr int kShortCalls = 4;
+// Short calls (fewer than kGraphSteps steps) are launched eagerly, which costs
+// the host less time than the GPU: a host that runs ahead hears of a full
+// bucket (host_flag) only after all it has queued.  After kGraphSteps steps
+// that it knows nothing of, the next one carries the re-bucketing kernels, which
+// end at once where no box needs them (about 25 us); contexts of more than
+// kBlindGrid workgroups, whose empty launches cost more, go without, their host
+// far ahead in any case.
+constexpr int64_t kBlindGrid = 4096;
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
@@ -120,10 +123,11 @@ struct mpcd_ctx {
     hipGraphExec_t graph_exec = nullptr;
     std::vector<Retired> retired;
 
-    // calls of fewer than kGraphSteps steps since the host last waited for the
-    // stream, and an event behind each but the first of the last kShortCalls
-    int64_t short_calls = 0;
-    hipEvent_t short_done[kShortCalls] = {};
+    // steps queued by short calls that the host does not know to have run, and
+    // those of them behind the event `mark` (recorded while it is `marked`)
+    int64_t blind = 0, after_mark = 0;
+    bool marked = false;
+    hipEvent_t mark = nullptr;
 
     // host-to-device uploads are stream-ordered through pinned staging
     std::vector<Upload> uploads;
@@ -539,6 +543,13 @@ int capture_graph(mpcd_ctx* c)
     c->graph = g;
     HIPCHK(hipGraphInstantiate(&c->graph_exec, g, nullptr, nullptr, 0));
     return MPCD_OK;
+}
+
+// Every step queued so far has run, or the next one re-buckets.
+void heard(mpcd_ctx* c)
+{
+    c->blind = 0;
+    c->marked = false;
 }
 
 Slot* live_slot(mpcd_ctx* c, int32_t slot)
@@ -1065,13 +1076,18 @@ int mpcd_step(mpcd_ctx* c, int32_t n)
         if (rc) return rc;
     }
     if (c->T.nactive == 0) return MPCD_OK;
-    const bool bounded = c->use_graph && !c->profiling && n < kGraphSteps;
-    if (bounded && c->short_calls >= kShortCalls)
-        HIPCHK(hipEventSynchronize(c->short_done[std::max<int64_t>(c->short_calls - kShortCalls, 1) % kShortCalls]));
+    const bool brief = c->use_graph && !c->profiling && n < kGraphSteps && c->any_brick &&
+                       (int64_t)c->T.nptiles + c->T.nctiles + c->T.nbtiles <= kBlindGrid;
+    if (brief && c->marked && hipEventQuery(c->mark) == hipSuccess) {
+        c->marked = false;
+        c->blind = c->after_mark;
+    }
     // a bucket overflowed in an earlier step: the boxes concerned carry the
     // rebucket flag; re-bucket them in the next step
     if (__atomic_exchange_n(c->host_flag, 0, __ATOMIC_ACQ_REL) != 0) c->pending_rebucket = true;
-    if (c->pending_rebucket) {   // bucket fresh brick boxes, then one eager step
+    const int32_t steps = n;
+    if (c->pending_rebucket || (brief && c->blind >= kGraphSteps)) {   // bucket fresh brick boxes, then one eager step
+        heard(c);
         int rc = enqueue_step(c, true);
         if (rc) return rc;
         c->pending_rebucket = false;
@@ -1094,13 +1110,16 @@ int mpcd_step(mpcd_ctx* c, int32_t n)
             if (rc) return rc;
         }
     }
-    if (bounded) {
-        if (c->short_calls > 0) {   // a step or two between calls that read the box leave no event
-            hipEvent_t& e = c->short_done[c->short_calls % kShortCalls];
-            if (!e) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-            HIPCHK(hipEventRecord(e, c->stream));
+    if (brief) {
+        if (c->marked) {
+            c->after_mark += steps;
+        } else if (c->blind > 0) {   // a step or two between calls that read the box leave no event
+            if (!c->mark) HIPCHK(hipEventCreateWithFlags(&c->mark, hipEventDisableTiming));
+            HIPCHK(hipEventRecord(c->mark, c->stream));
+            c->marked = true;
+            c->after_mark = 0;
         }
-        ++c->short_calls;
+        c->blind += steps;
     }
     return MPCD_OK;
 }
@@ -1116,7 +1135,7 @@ int mpcd_observe(mpcd_ctx* c, int32_t slot, mpcd_observables* out)
     int rc = take_snapshot(c, slot, false, c->report_dev);
     if (rc) return rc;
     HIPCHK(hipStreamSynchronize(c->stream));
-    c->short_calls = 0;
+    heard(c);
     const BoxState st = c->report->st;
     c->vacf_host.assign((size_t)std::max(st.vacf_len, 0), 0.0);
     if (st.vacf_len > 0 && st.vacf_len <= kReportVacf)
@@ -1161,7 +1180,7 @@ int mpcd_get_state(mpcd_ctx* c, int32_t slot, float* xyzv, int64_t* step)
         launch_state_by_id(c->T, slot, sl->dev.nslot, n, sl->part, c->report_dev, stage_dev, c->stream);
         HIPCHK(hipGetLastError());
         HIPCHK(hipStreamSynchronize(c->stream));
-        c->short_calls = 0;
+        heard(c);
         const BoxState& st = c->report->st;
         if (c->report->count != n) return MPCD_ESTATE;
         if (stage)
@@ -1498,8 +1517,7 @@ void mpcd_destroy(mpcd_ctx* c)
     if (c->report) (void)hipHostFree(c->report);
     if (c->state_stage) (void)hipHostFree(c->state_stage);
     for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
-    for (hipEvent_t e : c->short_done)
-        if (e) (void)hipEventDestroy(e);
+    if (c->mark) (void)hipEventDestroy(c->mark);
     if (c->own_stream) (void)hipStreamDestroy(c->stream);
     delete c;
 }

@@ -106,3 +106,46 @@ def test_vacf_of_many_fast_particles(mp, binning, brick, more):
     print("[vacf]", obs["vacf"], flush=True)
     assert len(obs["vacf"]) == 4
     assert np.all(np.abs(obs["vacf"] - 3.0 * speed ** 2) <= 1e-5 * 3.0 * speed ** 2)
+
+
+def test_short_steps_do_not_wait(mp):
+    """mpcd_step queues its work and returns, however many calls are queued."""
+    import time
+    L = (256, 256, 256)
+    with mp.Context() as ctx:
+        ctx.admit(mp.make_desc(L, 10 * L[0] * L[1] * L[2], seed=4, unordered=True))
+        ctx.step(20)
+        ctx.step(1)
+        ctx.synchronize()
+        t0 = time.perf_counter()
+        for _ in range(24):   # about 2 ms of work each
+            ctx.step(1)
+        t1 = time.perf_counter()
+        ctx.synchronize()
+        t2 = time.perf_counter()
+    print("[async] queued in %.2f ms, run in %.2f ms" % ((t1 - t0) * 1e3, (t2 - t0) * 1e3), flush=True)
+    assert t1 - t0 < 0.5 * (t2 - t0)
+
+
+@pytest.mark.parametrize("per_call", [1, 3, 15])
+def test_overflow_is_heard_of_while_the_host_runs_ahead(mp, per_call):
+    """Short calls without a wait between them: full buckets are laid out anew
+    all the same, and the trajectory is that of counting-sort binning."""
+    L, n = (16, 16, 16), 20000
+    g = np.random.default_rng(31)
+    pos = (g.uniform(0.0, 1.0, (3, n)) * np.array([[3.0], [16.0], [16.0]])).astype(np.float32)
+    vel = g.standard_normal((3, n)).astype(np.float32)
+    vel[0] += np.float32(4.0)
+    out, obs = [], []
+    for binning in (mp.MPCD_BIN_ATOMIC, mp.MPCD_BIN_SORT):
+        with mp.Context(binning=binning, brick=4) as ctx:
+            slot = ctx.admit(mp.make_desc(L, n, init="external", seed=3), (pos, vel))
+            for _ in range(45 // per_call):
+                ctx.step(per_call)
+            out.append(ctx.get_state(slot))
+            obs.append(ctx.observe(slot))
+    print("[ahead] steps with overflow %d, re-bucketings %d" % (obs[0]["overflow_steps"], obs[0]["rebuckets"]),
+          flush=True)
+    assert obs[0]["overflow_steps"] > 0 and obs[0]["rebuckets"] >= 2
+    assert out[0][2] == 45
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
