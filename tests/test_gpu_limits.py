@@ -149,3 +149,35 @@ def test_overflow_is_heard_of_while_the_host_runs_ahead(mp, per_call):
     assert obs[0]["overflow_steps"] > 0 and obs[0]["rebuckets"] >= 2
     assert out[0][2] == 45
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+
+
+def test_overflow_beside_a_sort_binned_box(mp):
+    """One context with both forms (bricks of 2^3 cells give a box of 1024^3
+    cells more slots than bucket starts can count, so it is sort-binned): buckets
+    overflow inside a call, in graphs that sort every step, and between calls.
+    Both boxes end where they end alone."""
+    L, n = (16, 16, 16), 20000
+    g = np.random.default_rng(31)
+    pos = (g.uniform(0.0, 1.0, (3, n)) * np.array([[3.0], [16.0], [16.0]])).astype(np.float32)
+    vel = g.standard_normal((3, n)).astype(np.float32)
+    vel[0] += np.float32(4.0)
+    wide = mp.make_desc((1024, 1024, 1024), 3000, seed=9)
+    slab = mp.make_desc(L, n, init="external", seed=3)
+    calls = (20, 1, 2, 33, 5)
+    with mp.Context(binning=mp.MPCD_BIN_ATOMIC, brick=2) as ctx:
+        a, b = ctx.admit(wide), ctx.admit(slab, (pos, vel))
+        for steps in calls:
+            ctx.step(steps)
+        seen, obs = [ctx.get_state(s) for s in (a, b)], [ctx.observe(s) for s in (a, b)]
+    assert [o["binning"] for o in obs] == [mp.MPCD_BIN_SORT, mp.MPCD_BIN_ATOMIC]
+    print("[both] steps with overflow %d, re-bucketings %d" % (obs[1]["overflow_steps"], obs[1]["rebuckets"]),
+          flush=True)
+    assert obs[1]["overflow_steps"] > 0 and obs[1]["rebuckets"] >= 3   # (on the device: the host is ahead)
+    for i, (desc, state) in enumerate(((wide, None), (slab, (pos, vel)))):
+        with mp.Context(binning=mp.MPCD_BIN_SORT) as ctx:
+            s = ctx.admit(desc, state)
+            for steps in calls:
+                ctx.step(steps)
+            p, v, k = ctx.get_state(s)
+        assert k == seen[i][2] == sum(calls)
+        assert np.array_equal(p, seen[i][0]) and np.array_equal(v, seen[i][1])
