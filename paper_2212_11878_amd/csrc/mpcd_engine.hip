@@ -674,14 +674,19 @@ int mpcd::validate_box_desc(const mpcd_box_desc* d) { return validate_desc(d); }
 // replaces the rule's shape only when clearly faster.  Results do not depend
 // on the choice (cell sums are exact), only the speed does.
 
+// Thermal displacement of one step in cells.
+static double step_length(const mpcd_box_desc* d)
+{
+    return d->dt * (d->kT > 0 ? std::sqrt(d->kT / d->mass) : 1.0) / d->a;
+}
+
 static uint64_t shape_class(const mpcd_box_desc* d)
 {
     const double C = (double)d->L[0] * d->L[1] * d->L[2];
     const int lc = (int)std::floor(std::log2(std::max(1.0, C)));
     const double dens = std::max(1e-3, (double)d->n_particles / C);
     const int rho = (int)std::lround(std::min(255.0, std::max(0.0, 2.0 * std::log2(dens) + 20.0)));
-    const double vth = d->kT > 0 ? std::sqrt(d->kT / d->mass) : 1.0;
-    const int step = (int)std::min(15.0, std::floor(8.0 * d->dt * vth / d->a));   // free path / cell
+    const int step = (int)std::min(15.0, std::floor(8.0 * step_length(d)));   // free path / cell
     const uint64_t rule = (d->flags & MPCD_CONSERVE_L) ? 1 : 0;   // angular-momentum rule
     const uint64_t ids = (d->flags & MPCD_UNORDERED) ? 0 : 1;     // particle ids travel
     return (ids << 33) | (rule << 32) | ((uint64_t)lc << 16) | ((uint64_t)rho << 4) | (uint64_t)step;
@@ -754,6 +759,23 @@ static int rule_shape(double density, bool am)
     return best;
 }
 
+// Few particles of bricks g pass beyond the neighbouring bricks in a step (they
+// are placed one at a time): none where a dimension has at most three bricks,
+// else the displacement is short of 0.55 brick edges.  Measured per step
+// of a box alone, density 10: 10^3 cells, displacement 1: bricks of 2^3 12.2 us, of
+// 4^3 12.8; 2: 16.4 and 13.0; 16^3 cells, 1: 4x2x2 12.4, 4^3 13.3; 1.5: 16.4 and
+// 14.1; density 2.5, 32^3 cells, 2: 8x4x4 13.7, 8^3 16.9; 4: 30.6 and 23.4.  Where
+// no brick reaches, small ones are faster again (density 10, 16^3 cells, 4:
+// 4x2x2 29 us, 8x4x4 45), and so they are throughout under the angular-momentum rule,
+// whose cell work they spread (12^3 cells, 2: 2^3 25.7 us, 4^3 31.2).
+static bool within_reach(const mpcd_box_desc* d, const BrickGeom& g)
+{
+    const double step = step_length(d);
+    for (int k = 0; k < 3; ++k)
+        if (g.nb[k] > 3 && step > 0.55 * (1 << g.shift[k])) return false;
+    return true;
+}
+
 static int autotune(mpcd_ctx* c, const mpcd_box_desc* d, int32_t* binning, int32_t brick[3])
 {
     const double C = (double)d->L[0] * d->L[1] * d->L[2];
@@ -761,15 +783,26 @@ static int autotune(mpcd_ctx* c, const mpcd_box_desc* d, int32_t* binning, int32
     const bool am = (d->flags & MPCD_CONSERVE_L) != 0;
     int r = rule_shape(density, am);
     // while every brick of the context has a CU of its own, smaller bricks
-    // shorten the step (more, shorter workgroups); boxes that join a larger
-    // batch keep the rule's, which cost less in all.  (Smaller bricks need more
-    // spare slots: not under a memory budget, which admits what it did.)
+    // shorten the step (more, shorter workgroups), down to the smallest that
+    // most particles do not fly past; boxes that join a larger batch keep the
+    // rule's, which cost less in all.  (Smaller bricks need more spare slots: not
+    // under a memory budget, which admits what it did.)
     if (!c->tuning && c->budget == 0) {
         int64_t live = 0;
         for (const Slot& sl : c->slots)
             if (sl.live) live += sl.dev.nbrick;
-        for (int i = 0; i < r; ++i)
-            if (rule_allowed(i, am) && live + brick_geometry(d->L, kRuleShapes[i]).nbrick <= kSmallGrid) r = i;
+        int small = -1;   // the smallest brick that fits, or the smallest within reach
+        for (int i = 0; i < r; ++i) {
+            const BrickGeom g = brick_geometry(d->L, kRuleShapes[i]);
+            if (!rule_allowed(i, am) || live + g.nbrick > kSmallGrid) continue;
+            if (small < 0) small = i;
+            if (am || within_reach(d, g)) {
+                r = i;
+                small = -1;
+                break;
+            }
+        }
+        if (small >= 0 && !within_reach(d, brick_geometry(d->L, kRuleShapes[r]))) r = small;
     }
     // defaults, also used inside trial contexts, for empty and for small boxes
     *binning = MPCD_BIN_ATOMIC;

@@ -181,3 +181,26 @@ def test_overflow_beside_a_sort_binned_box(mp):
             p, v, k = ctx.get_state(s)
         assert k == seen[i][2] == sum(calls)
         assert np.array_equal(p, seen[i][0]) and np.array_equal(v, seen[i][1])
+
+
+@pytest.mark.parametrize("L,density,more,brick", [
+    (10, 10, dict(dt=0.1), (2, 2, 2)),
+    (10, 10, dict(dt=2.0), (4, 4, 4)),            # particles would fly past bricks of 2^3
+    (10, 10, dict(dt=1.0, kT=4.0), (4, 4, 4)),
+    (10, 10, dict(dt=2.0, a=2.0), (2, 2, 2)),
+    (32, 2.5, dict(dt=4.0), (8, 8, 8)),
+    (16, 10, dict(dt=4.0), (4, 2, 2)),            # out of reach of every brick
+    (12, 10, dict(dt=2.0, conserve_l=True), (2, 2, 2)),
+])
+def test_bricks_of_a_box_alone_reach_a_step(mp, L, density, more, brick):
+    """A box alone in its context gets the smallest bricks that a step's
+    displacement does not pass, and the bits of counting-sort binning."""
+    n = int(density * L ** 3)
+    out = []
+    for binning in (mp.MPCD_BIN_AUTO, mp.MPCD_BIN_SORT):
+        with mp.Context(binning=binning) as ctx:
+            slot = ctx.admit(mp.make_desc(L, n, seed=3, **more))
+            ctx.step(5)
+            out.append((ctx.get_state(slot), ctx.observe(slot)))
+    assert out[0][1]["brick"] == brick
+    assert np.array_equal(out[0][0][0], out[1][0][0]) and np.array_equal(out[0][0][1], out[1][0][1])
