@@ -625,7 +625,11 @@ float* state_stage(mpcd_ctx* c, int64_t n, float** dev)
         else
             c->stage_cap = (size_t)n * 24;
     }
-    if (!c->state_stage || hipHostGetDevicePointer((void**)dev, c->state_stage, 0) != hipSuccess) return nullptr;
+    if (!c->state_stage || hipHostGetDevicePointer((void**)dev, c->state_stage, 0) != hipSuccess) {
+        (void)hipGetLastError();   // the caller copies instead: not its launches' error
+        *dev = nullptr;
+        return nullptr;
+    }
     return c->state_stage;
 }
 
