@@ -463,6 +463,18 @@ __host__ __device__ __forceinline__ StatRuns stat_runs(int ntile)
     return StatRuns{ntile, p, ntile < 2 * p ? 1 : ntile / p};
 }
 
+// A 128-bit sum as two of the 64-bit words it is kept over (low word first; a
+// run of an odd number of tiles starts on no multiple of 16 bytes).
+__host__ __device__ __forceinline__ void stat_put(long long* p, __int128 v)
+{
+    p[0] = (long long)(unsigned long long)v;
+    p[1] = (long long)(v >> 64);
+}
+__host__ __device__ __forceinline__ __int128 stat_get(const long long* p)
+{
+    return (__int128)(((unsigned __int128)(unsigned long long)p[1] << 64) | (unsigned long long)p[0]);
+}
+
 // Spare slots given to a bucket that re-bucketing found holding n
 // particles: the bucket's size wanders like a Poisson count, so the margin
 // is about 4 standard deviations plus 1/8 and a constant.

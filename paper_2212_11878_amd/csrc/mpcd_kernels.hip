@@ -2271,7 +2271,7 @@ __global__ __launch_bounds__(kStatBlock) void k_box_stats(const long long* __res
     if (packed) {
         const int j = threadIdx.x % kNumDiag;
         for (int t = threadIdx.x / kNumDiag; t < nitems; t += kStatBlock / kNumDiag) {
-            const __int128 q = reinterpret_cast<const __int128*>(partials + (size_t)t * per * kNumDiag)[j];
+            const __int128 q = stat_get(partials + (size_t)t * per * kNumDiag + 2 * j);
             hi += (long long)(q >> 32);
             lo += (unsigned long long)(q & 0xffffffff);
         }
@@ -2300,8 +2300,7 @@ __global__ __launch_bounds__(kStatBlock) void k_box_stats_tiles(long long* __res
     stat_share(partials + (size_t)t0 * kNumDiag, t1 - t0, hi, lo);
     stat_totals(hi, lo, tot);   // its barriers: every thread has read its tiles before thread 0 overwrites two
     if (threadIdx.x == 0) {
-        __int128* q = reinterpret_cast<__int128*>(partials + (size_t)t0 * kNumDiag);
-        for (int j = 0; j < kNumDiag; ++j) q[j] = tot[j];
+        for (int j = 0; j < kNumDiag; ++j) stat_put(partials + (size_t)t0 * kNumDiag + 2 * j, tot[j]);
     }
 }
 
