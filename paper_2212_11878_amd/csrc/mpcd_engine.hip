@@ -157,7 +157,10 @@ void* ctx_alloc(mpcd_ctx* c, size_t bytes)
     if (bytes == 0) bytes = 256;
     if (c->alloc) return c->alloc(bytes, c->user);
     void* p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
+    if (hipMalloc(&p, bytes) != hipSuccess) {
+        (void)hipGetLastError();   // the caller's ENOMEM: not an error of the next launch
+        return nullptr;
+    }
     return p;
 }
 

@@ -1,8 +1,10 @@
-/* A C client in which pinned host memory runs out after the context exists:
- * its own hipHostMalloc (taken for the runtime's, which it calls until then)
- * fails and leaves the runtime's error recorded, as the runtime's does.  State
- * transfers then go by the plain copies.  Prints "ok" or the first failed
- * check; exit status 0 ok, 1 a failed check, 77 no usable device. */
+/* A C client in which memory runs out after the context exists: its own
+ * hipHostMalloc and hipMalloc (taken for the runtime's, which they call until
+ * then) fail and leave the runtime's error recorded, as the runtime's do.
+ * Without pinned memory state transfers go by the plain copies; without device
+ * memory an admission fails, and the boxes admitted before run on.  Prints "ok"
+ * or the first failed check; exit status 0 ok, 1 a failed check, 77 no usable
+ * device. */
 #define _GNU_SOURCE
 #include <dlfcn.h>
 #include <stdio.h>
@@ -26,6 +28,19 @@ int hipHostMalloc(void** p, size_t bytes, unsigned flags)
         return 2;                 /* hipErrorOutOfMemory */
     }
     return real(p, bytes, flags);
+}
+
+int hipMalloc(void** p, size_t bytes)
+{
+    int (*real)(void**, size_t);
+    *(void**)&real = dlsym(RTLD_NEXT, "hipMalloc");
+    if (exhausted) {
+        ++refused;
+        (void)hipSetDevice(-1);
+        *p = NULL;
+        return 2;
+    }
+    return real(p, bytes);
 }
 
 static int failed(const char* what, int rc)
@@ -73,6 +88,12 @@ int main(void)
     exhausted = 0;
     if ((rc = mpcd_get_state(ctx, slot, t, &step)) != MPCD_OK) return failed("get_state 3", rc);
     if (memcmp(s, t, sizeof(float) * 6 * (size_t)n) != 0) return failed("state", 0);
+    exhausted = 1;
+    int32_t other = -1;
+    if ((rc = mpcd_admit(ctx, &d, &other)) != MPCD_ENOMEM) return failed("admit without memory", rc);
+    if (refused < 4) return failed("refusals 2", refused);
+    if ((rc = mpcd_step(ctx, 20)) != MPCD_OK) return failed("step after it", rc);
+    if ((rc = mpcd_observe(ctx, slot, &o)) != MPCD_OK || o.step != 24) return failed("observe after it", rc);
     mpcd_destroy(ctx);
     free(s);
     free(t);
