@@ -121,25 +121,25 @@ __device__ __forceinline__ void block_diag(long long (&d)[kNumDiag], long long* 
     }
 }
 
-// A wave's share of the box's VACF sum, at most 8192 terms below 3 2^48, into
-// the box's accumulators: high and low 32-bit halves, so no lane can overflow.
-// Atomic integer adds are exact, so the order does not matter; the workgroups
-// are spread over kAccLanes lanes per box.
-__device__ __forceinline__ void vacf_flush_wave(long long vsum, long long* acc, int lane_sel)
+// A wave's share of the box's VACF sum into the box's accumulators: each
+// thread's as hi 2^32 + lo, so that no sum over threads can overflow.  Atomic
+// integer adds are exact, so the order does not matter; the workgroups are
+// spread over kAccLanes lanes per box.
+__device__ __forceinline__ void vacf_flush_wave(long long hi, long long lo, long long* acc, int lane_sel)
 {
-    long long* a = acc + (size_t)(lane_sel & (kAccLanes - 1)) * 3;
-    const long long v = wave_sum(vsum);
+    hi = wave_sum(hi);
+    lo = wave_sum(lo);
     if ((threadIdx.x & (kWave - 1)) == 0) {
-        gatomic_add(gp(a), v >> 32);
-        gatomic_add(gp(a) + 1, (long long)(unsigned long long)(unsigned)(v & 0xffffffffll));
+        MPCD_G long long* const a = gp(acc) + (size_t)(lane_sel & (kAccLanes - 1)) * 3;
+        gatomic_add(a, hi);
+        gatomic_add(a + 1, lo);
     }
 }
+__device__ __forceinline__ long long low_word(long long v) { return v & 0xffffffffll; }
 
-// End of a wave of a step kernel: what is left of its VACF sum (on sampled
-// steps) and its range-violation mark.
-__device__ __forceinline__ void step_flush_wave(bool viol, long long vsum, bool vacf, long long* acc, int lane_sel)
+// The same for its range-violation mark.
+__device__ __forceinline__ void mark_flush_wave(bool viol, long long* acc, int lane_sel)
 {
-    if (vacf) vacf_flush_wave(vsum, acc, lane_sel);
     if (__any(viol) && (threadIdx.x & (kWave - 1)) == 0)
         gatomic_add(gp(acc) + (size_t)(lane_sel & (kAccLanes - 1)) * 3 + 2, 1ll);
 }
@@ -778,7 +778,10 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t wave = (uint32_t)uniform((int)(threadIdx.x / kWave));
     const unsigned long long below = (1ull << lane) - 1ull;
-    long long vsum = 0;   // VACF terms
+    // VACF terms, modulo 2^64, and the sum of their parts from 2^40 up: the rest
+    // of up to 2^21 terms, the difference, is below 2^61
+    unsigned long long vsum = 0ull;
+    uint32_t vtop = 0u;
     const bool vacf = kIds && b.vacf_stride > 0 && ((k + 1 - uniform(s.vacf_origin)) % b.vacf_stride) == 0;
     for (int ch = 0; ch < nch; ++ch) {
         if (ch > 0) {
@@ -924,7 +927,8 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
                 if (index_of(ch, u) >= cnt) continue;
                 long long d[kNumDiag] = {};
                 vacf_term(b, id[u], make_float3(vx[u], vy[u], vz[u]), d);
-                vsum += d[4];
+                vsum += (unsigned long long)d[4];
+                vtop += (uint32_t)(d[4] >> 40);
             }
         }
         while (miss) {   // far (or full) destination, one at a time
@@ -943,15 +947,14 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
             if (placed) store_at(j, x, y, z, v, kIds ? pick(id, u) : 0, m);
             else viol = 1u;
         }
-        if (ch + 1 < nch) {
-            if (kIds && vacf) {   // (a wave's chunk has at most 512 terms)
-                vacf_flush_wave(vsum, dacc + (size_t)uniform(tl.box) * kAccLanes * 3, blockIdx.x);
-                vsum = 0;
-            }
-            __syncthreads();
-        }
+        if (ch + 1 < nch) __syncthreads();
     }
-    step_flush_wave(viol != 0u, vsum, vacf, dacc + (size_t)uniform(tl.box) * kAccLanes * 3, blockIdx.x);
+    long long* const box_acc = dacc + (size_t)uniform(tl.box) * kAccLanes * 3;
+    if (kIds && vacf) {
+        const long long top = (int)vtop, rest = (long long)(vsum - ((unsigned long long)top << 40));
+        vacf_flush_wave(top * 256 + (rest >> 32), low_word(rest), box_acc, blockIdx.x);
+    }
+    mark_flush_wave(viol != 0u, box_acc, blockIdx.x);
 }
 
 // Particles of the overflow bucket of the current buffer (one workgroup per
@@ -1001,7 +1004,7 @@ __device__ uint32_t overflow_step(const BoxDev& b, const BoxState& s, long long 
             d[4] = 0;
             vacf_term(b, id, v, d);
             hi += d[4] >> 32;
-            lo += (long long)(unsigned long long)(unsigned)(d[4] & 0xffffffffll);
+            lo += low_word(d[4]);
         }
         put_particle(b, dst, j, x, y, z, v, id, m, has_m);
     }
@@ -1603,20 +1606,12 @@ void k_cell_rotate(const Tile* __restrict__ tiles, const BoxDev* __restrict__ bo
                 collide_cell_am(b, par, k, cell_of_key(b.L, b.sshift, (uint32_t)c), beg, end, sh, b.ca, b.sa, d, vacf);
             if (vacf) {   // split after every cell (fewer than kMaxCellCount terms)
                 hi += d[4] >> 32;
-                lo += (long long)(unsigned long long)(unsigned)(d[4] & 0xffffffffll);
+                lo += low_word(d[4]);
                 d[4] = 0;
             }
         }
-        if (vacf) {
-            hi = wave_sum(hi);
-            lo = wave_sum(lo);
-            if ((threadIdx.x & (kWave - 1)) == 0) {
-                MPCD_G long long* const a = gp(acc) + (size_t)(blockIdx.x & (kAccLanes - 1)) * 3;
-                gatomic_add(a, hi);
-                gatomic_add(a + 1, lo);
-            }
-        }
-        step_flush_wave(d[5] != 0, 0, false, acc, blockIdx.x);
+        if (vacf) vacf_flush_wave(hi, lo, acc, blockIdx.x);
+        mark_flush_wave(d[5] != 0, acc, blockIdx.x);
         return;
     }
     // the particles of the next buffer's slots come from the current buffer
@@ -1710,16 +1705,6 @@ void k_cell_rotate(const Tile* __restrict__ tiles, const BoxDev* __restrict__ bo
         gather(r.np);
     }
     if (fits(r2)) load_perm(r2.base, r2.np);
-    // A run leaves a wave kRotCap / 4 VACF terms, an oversized cell fewer than
-    // kMaxCellCount.
-    int runs = 0;
-    auto flush_runs = [&](int n) {
-        runs += n;
-        if (!vacf || runs < 16) return;
-        vacf_flush_wave(d[4], acc, blockIdx.x);
-        d[4] = 0;
-        runs = 0;
-    };
     while (r.c < nc) {
         const int c = r.c, e = r.e;
         const uint32_t base = r.base, np = r.np;
@@ -1741,7 +1726,10 @@ void k_cell_rotate(const Tile* __restrict__ tiles, const BoxDev* __restrict__ bo
             if (threadIdx.x == 0)
                 collide_cell_serial(b, par, k, cell_of_key(b.L, b.sshift, (uint32_t)(tl.begin + c)), base, cs[e], d,
                                     vacf);
-            flush_runs(16);
+            if (vacf) {   // (fewer than kMaxCellCount terms of one thread; the runs leave it at most 8192)
+                vacf_flush_wave(d[4] >> 32, low_word(d[4]), acc, blockIdx.x);
+                d[4] = 0;
+            }
             r = r2;
             r2 = run_at(r.e);
             if (fits(r)) gather(r.np);
@@ -1843,11 +1831,11 @@ void k_cell_rotate(const Tile* __restrict__ tiles, const BoxDev* __restrict__ bo
             if (vacf) vacf_term(b, pid[base + j], v, d);
         }
         __syncthreads();   // the staging area is refilled by the next run
-        flush_runs(1);
         r = r2;
         r2 = r3;
     }
-    step_flush_wave(d[5] != 0, d[4], vacf, acc, blockIdx.x);
+    if (vacf) vacf_flush_wave(d[4] >> 32, low_word(d[4]), acc, blockIdx.x);
+    mark_flush_wave(d[5] != 0, acc, blockIdx.x);
 }
 
 // --------------------------------------------------------------------------
