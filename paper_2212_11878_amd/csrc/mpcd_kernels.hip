@@ -552,6 +552,12 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
         return min(gp(b.bsize[src])[nbk], gp(b.bstart)[nbk + 1] - gp(b.bstart)[nbk]);
     };
     const bool fp64 = (kAM && am) ? !has_mass : !kMass;   // equal masses
+    auto add_ints = [&](unsigned long long* r, float ux, float uy, float uz) {
+        atomicAdd(&r[0], to_fixed(ux));
+        atomicAdd(&r[1], to_fixed(uy));
+        atomicAdd(&r[2], to_fixed(uz));
+        atomicAdd(reinterpret_cast<uint32_t*>(&r[3]), 1u);
+    };
     // From memory: the particles of the slots [first, first + n) whose collision
     // cell lies in this brick.  Pass 1 sums (plain rule: integers; `ints` as in
     // am_add), pass 2 adds their angular-momentum change.
@@ -576,11 +582,7 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
                 if (pass == 1) am_add(ra, ints, mj, ux, uy, uz, rl);
                 else if (!am_add_dl(ra, mj, ux, uy, uz, rl, b.ca, b.sa)) viol = 1u;
             } else {
-                unsigned long long* const r = acc + c * kAccWords;
-                atomicAdd(&r[0], to_fixed(ux));
-                atomicAdd(&r[1], to_fixed(uy));
-                atomicAdd(&r[2], to_fixed(uz));
-                atomicAdd(reinterpret_cast<uint32_t*>(&r[3]), 1u);
+                add_ints(acc + c * kAccWords, ux, uy, uz);
             }
         }
     };
@@ -605,7 +607,22 @@ void k_brick_step(const Tile* __restrict__ tiles, int one_box, const BoxDev* __r
                 ints = true;
                 for (int i = threadIdx.x; i < (am ? kAmWords : kAccWords) * ncl; i += kT) lds64[i] = 0ull;
                 __syncthreads();
-                add_slots(beg, cnt, 1, true);
+                if (kAM) {
+                    add_slots(beg, cnt, 1, true);
+                } else {   // (through the pointers at hand: others cost every step registers)
+#pragma unroll 1
+                    for (uint32_t i = threadIdx.x; i < cnt; i += kT) {
+                        const float ux = ldg(ivx, i * 4u), uy = ldg(ivy, i * 4u), uz = ldg(ivz, i * 4u);
+                        const float qx = fold(fmaf(ux, dt, ldg(ix, i * 4u)), len0);
+                        const float qy = fold(fmaf(uy, dt, ldg(iy, i * 4u)), len1);
+                        const float qz = fold(fmaf(uz, dt, ldg(iz, i * 4u)), len2);
+                        const int cx = axis_cell(qx, sh.x, inv_a, b.L[0]) - lox;
+                        const int cy = axis_cell(qy, sh.y, inv_a, b.L[1]) - loy;
+                        const int cz = axis_cell(qz, sh.z, inv_a, b.L[2]) - loz;
+                        if ((unsigned)cx < (unsigned)ex && (unsigned)cy < (unsigned)ey && (unsigned)cz < (unsigned)ez)
+                            add_ints(acc + (cx + ex * (cy + ey * cz)) * kAccWords, ux, uy, uz);
+                    }
+                }
                 __syncthreads();
             }
         }
