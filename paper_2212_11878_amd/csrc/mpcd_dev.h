@@ -36,8 +36,8 @@ constexpr int kPartTile = 4096;      // particles per particle tile (16 per thre
 constexpr int kCellTile = 2048;      // cells per cell tile
 constexpr int kMaxBrickCells = 1024; // cells of one brick (LDS of its workgroup)
 constexpr int kSortBlockShift = 4;    // the counting sort orders cells in blocks of 16^3
-constexpr int kAccWords = 5;         // 64-bit words per brick cell's sums record (4 used)
-constexpr int kUnWords = 12;         // 32-bit words per brick cell's data record (7 used)
+constexpr int kAccWords = 5;         // 64-bit words per brick cell's sums record (equal masses use 4)
+constexpr int kUnWords = 12;         // 32-bit words per brick cell's data record (CellRot)
 constexpr int kBrickCellBytes = 8 * kAccWords + 4 * kUnWords;   // LDS per brick cell
 // Angular-momentum-conserving collision on bricks: per cell 18 64-bit LDS
 // words (first the 13 moment sums, then u, r_c, n, Q / omega in FP64 and the
@@ -140,7 +140,7 @@ struct BoxState {
     long long vacf_origin; // step at which v0 was taken
     int parity;            // particle buffer in use
     int vacf_len;
-    int status;            // 0 or MPCD_ESTATE
+    int status;            // 0 or MPCD_ESTATE (marked: a velocity out of range, a crowded cell)
     int rebucket;          // brick mode: buckets to be rebuilt by the counting sort
     long long overflow_steps;   // brick mode: steps in which a bucket was full
     long long rebuckets;        // brick mode: re-bucketings done
@@ -779,8 +779,8 @@ __host__ __device__ __forceinline__ void diag_check(long long (&d)[kNumDiag], fl
     if (!in_range(v)) d[5] += 1;
 }
 
-// VACF term v . v0, below 3 2^48 in fixed point, so a workgroup's sum of at
-// most 4096 terms stays below 2^62
+// VACF term v . v0, below 3 2^48 in fixed point, so a sum of kPartTile terms
+// stays below 2^62
 __device__ __forceinline__ void diag_vacf(long long (&d)[kNumDiag], float3 v, float w0x, float w0y,
                                           float w0z)
 {

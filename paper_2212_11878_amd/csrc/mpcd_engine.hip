@@ -118,7 +118,7 @@ struct mpcd_ctx {
     bool dirty = true;
     bool any_brick = false, any_sort = false;
 
-    // graph of one step
+    // graph of kGraphSteps steps
     hipGraph_t graph = nullptr;
     hipGraphExec_t graph_exec = nullptr;
     std::vector<Retired> retired;
@@ -675,7 +675,8 @@ int mpcd::validate_box_desc(const mpcd_box_desc* d) { return validate_desc(d); }
 // ==========================================================================
 // Autotuner: picks the binning (brick or sort) and the brick shape.  Boxes
 // below 2^21 cells, and boxes whose buffers reach 2^30 slots, take the shape
-// the density rule gives; for the others a class of boxes is timed once on
+// the density rule gives (small boxes alone in a context smaller ones); for the
+// others a class of boxes is timed once on
 // short trial runs of a proxy box of the same density and time step (at most
 // 128^3 cells) in a private context on the same stream, and a candidate
 // replaces the rule's shape only when clearly faster.  Results do not depend

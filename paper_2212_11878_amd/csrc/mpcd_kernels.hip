@@ -103,10 +103,9 @@ __device__ __forceinline__ Tile box_tile(const BoxDev* __restrict__ boxes, int b
 }
 
 // Block sum of kNumDiag exact partials; threads 0..kNumDiag-1 write out[].
-template <int kT = kBlock>
 __device__ __forceinline__ void block_diag(long long (&d)[kNumDiag], long long* out)
 {
-    __shared__ long long red[kT / kWave][kNumDiag];
+    __shared__ long long red[kBlock / kWave][kNumDiag];
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
 #pragma unroll
     for (int j = 0; j < kNumDiag; ++j) {
@@ -116,7 +115,7 @@ __device__ __forceinline__ void block_diag(long long (&d)[kNumDiag], long long* 
     __syncthreads();
     if (threadIdx.x < kNumDiag) {
         long long v = 0;
-        for (int i = 0; i < kT / kWave; ++i) v += red[i][threadIdx.x];
+        for (int i = 0; i < kBlock / kWave; ++i) v += red[i][threadIdx.x];
         out[threadIdx.x] = v;
     }
 }
@@ -315,31 +314,6 @@ __device__ __forceinline__ double exact_term(float v)
     return (double)truncf(v * kQ);
 }
 
-// One SRD step of one brick (paper Sec. 2; the shifted grid of Sec. 3.1;
-// the mass-weighted cell velocity of Sec. 3.3).  The workgroup owns every
-// particle whose collision cell lies in its brick, so the whole step is one
-// pass over them, held in registers (kS per thread; larger buckets take
-// several chunks, re-read from memory):
-//   1. stream, collision cell, exact cell sums in LDS (+ escape sums of
-//      overflow particles, when flagged)
-//   2. per cell: u_c = sum(m v)/sum(m), axis n_c from Philox (in place)
-//   3. rotate v about n_c relative to u_c; collision cell of the next step;
-//      rank in the destination group (27 neighbour bricks: wave ballots for
-//      the particles that stay, LDS counters for the others)
-//   4. one global reservation per group in the destination buckets, then
-//      stores.  Per step only the range check (and the VACF sum when a
-//      sample is due) is reduced; momentum and energy are summed on demand.
-// Each phase first takes the common case of every slot without a branch (the
-// particle stays inside the box and its cell needs no periodic wrap); the
-// slots that fail it are redone one at a time by a loop that holds the only
-// copy of the exact general form.  With a fold, a wrap and a far branch in
-// line for every slot and coordinate the kernel had twice the instructions
-// (58 KB of code): 256^3 box without ids 2.02 -> 1.97 ms a step, 203 x 167 x
-// 131 cells with ids 0.528 -> 0.49 ms, 100^3 with ids 157 -> 145 us.  What
-// bounds it is HBM: 48 B a particle, and the workgroup's chain of loads, cell
-// sums, reservation and stores, of which 5 per CU overlap.
-// The instance for equal masses without particle ids is held to 5 waves per
-// SIMD (96 registers), those with ids or 8 slots per thread to 4.
 // Angular-momentum rule: one particle's terms of the first pass into its
 // cell's record, as 64-bit integers (`ints`: per-particle masses, and where
 // exact_term does not hold) or, for mass 1, in FP64 (rounded to integers below
@@ -378,6 +352,32 @@ __device__ __forceinline__ bool am_add_dl(unsigned long long* ra, float m, float
 // Waves per SIMD of the angular-momentum instances.
 constexpr int am_waves(int slots) { return slots > 6 ? 3 : 4; }
 
+// One SRD step of one brick (paper Sec. 2; the shifted grid of Sec. 3.1;
+// the mass-weighted cell velocity of Sec. 3.3).  The workgroup owns every
+// particle whose collision cell lies in its brick, so the whole step is one
+// pass over them, held in registers (kS per thread; larger buckets take
+// several chunks, re-read from memory):
+//   1. stream, collision cell, exact cell sums in LDS (+ escape sums of
+//      overflow particles, when flagged; the sums of marked boxes and crowded
+//      cells once more, in integers)
+//   2. per cell: u_c = sum(m v)/sum(m), axis n_c from Philox (in place)
+//   3. rotate v about n_c relative to u_c; collision cell of the next step;
+//      rank in the destination group (27 neighbour bricks: wave ballots for
+//      the particles that stay, LDS counters for the others)
+//   4. one global reservation per group in the destination buckets, then
+//      stores.  Per step only the range check (and the VACF sum when a
+//      sample is due) is reduced; momentum and energy are summed on demand.
+// Each phase first takes the common case of every slot without a branch (the
+// particle stays inside the box and its cell needs no periodic wrap); the
+// slots that fail it are redone one at a time by a loop that holds the only
+// copy of the exact general form.  With a fold, a wrap and a far branch in
+// line for every slot and coordinate the kernel had twice the instructions
+// (58 KB of code): 256^3 box without ids 2.02 -> 1.97 ms a step, 203 x 167 x
+// 131 cells with ids 0.528 -> 0.49 ms, 100^3 with ids 157 -> 145 us.  What
+// bounds it is HBM: 48 B a particle, and the workgroup's chain of loads, cell
+// sums, reservation and stores, of which 5 per CU overlap.
+// The instance for equal masses without particle ids is held to 5 waves per
+// SIMD (96 registers), those with ids or 8 slots per thread to 4.
 template <int kT, int kS, bool kMass, bool kAM, bool kWide, bool kIds>
 __global__ __launch_bounds__(kT)
 __attribute__((amdgpu_waves_per_eu(kAM ? am_waves(kS) : kMass ? 1 : (kIds || kS > 6 ? 4 : 5), kMass || kIds || kS > 6 ? 8 : 5)))
